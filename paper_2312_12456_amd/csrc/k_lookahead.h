@@ -120,9 +120,8 @@ __global__ __launch_bounds__(kMfmaThreads) void k_la_up_hidden_mfma(
 // layer of predictor l+1 on the matrix cores].  Dynamic LDS: the output layer's 64 KB of slots;
 // FC2's cross-wave sums live in the same region (a workgroup plays one role), so that two
 // workgroups fit a CU.
-template <int B>
-__global__ __launch_bounds__(kMfmaThreads) void k_la_down_out_mfma(
-    int tiles, int P, const __half *__restrict__ w_down, const float *__restrict__ b_down,
+__global__ __launch_bounds__(kMfmaThreads, 4) void k_la_down_out_mfma(
+    int B, int hs, int tiles, int P, const __half *__restrict__ w_down, const float *__restrict__ b_down,
     const float *__restrict__ h, const int32_t *__restrict__ idx, const int32_t *__restrict__ count_p,
     float *__restrict__ part, int d, int ffn, const __half *__restrict__ p2,
     const float *__restrict__ p_bias, const float *__restrict__ t, int r, int ffn_next, float thr_logit,
@@ -130,12 +129,12 @@ __global__ __launch_bounds__(kMfmaThreads) void k_la_down_out_mfma(
 {
     extern __shared__ uint64_t dyn_lds64[];
     __shared__ float logit_s[16][64];
-    static_assert(sizeof(float) * kDown2Waves * B * kDown2Cols <= (size_t)kMfmaWaves * kRowsMfmaSlotBytes,
+    static_assert(sizeof(float) * kDown2mRedFloats <= (size_t)kMfmaWaves * kRowsMfmaSlotBytes,
                   "FC2's sums fit the slots");
     const int bid = (int)blockIdx.x, n_fc2 = tiles * P;
     if (bid < n_fc2) {  // uniform over the block
-        down2_body<B>(reinterpret_cast<float(*)[B][kDown2Cols]>(dyn_lds64), bid % tiles, bid / tiles, P, w_down,
-                      b_down, h, idx, count_p, part, d, ffn);
+        down2_mfma_body(reinterpret_cast<float *>(dyn_lds64), bid % tiles, bid / tiles, P, w_down, b_down,
+                        h, idx, count_p, part, B, hs, d, ffn);
     } else {
         rows_mfma_body<64, 64, 1, false>(dyn_lds64, logit_s, bid - n_fc2, p2, t, B, r, ffn_next, p_bias, thr_logit,
                                          nullptr, mask_next, first_word);

@@ -17,6 +17,7 @@
 #pragma once
 #include "dev_util.h"
 #include "k_predict.h"
+#include "k_sparse.h"
 
 namespace pf {
 
@@ -572,6 +573,169 @@ __global__ __launch_bounds__(kMfmaThreads) void k_rows_mfma(
     }
     rows_mfma_body<R, KC, EPI, XS>(dyn_lds64, logit_s, (int)blockIdx.x, w, v, B, K, nrows, p_bias, thr_logit,
                                out, mask_words, first_word);
+}
+
+// ---------------------------------------------------------------------------------------
+// FC2 over the listed neurons for a batch, on the matrix cores: y^T[column][token] =
+// sum over slots of W_down^T[row][column] * h[slot][token].  The vector form (down2_body) issues
+// 8 B + 12 vector instructions per 16-byte load; here it is about 30 whatever the batch.
+// Tiling of down2_body: a workgroup owns 64 columns (a whole 128-byte line per row) and every
+// P-th chunk of 64 list slots of each wave, and a lane loads 16 bytes (columns 8 cl .. 8 cl + 7,
+// cl = lane % 8) of each of 8 rows.  No LDS and no cross-lane step stands between these loads and
+// the matrix cores: for column t of its eight a lane collects the t-th halfs of its 8 rows (4
+// byte permutes) and has one MFMA operand -- M row lane % 16 = (row slot parity, column group
+// cl), K = the 8 rows in each of 4 lane groups.  The two row-slot parities share M and N: rows
+// m < 8 belong to even row slots and need tokens n < 8, rows m >= 8 to odd ones and n >= 8, so
+// B's columns carry h of the even slots' rows for tokens 0..7, then of the odd slots' rows.
+// The two off-diagonal 8 x 8 blocks of the result are not used (the matrix cores have room:
+// 16 MFMAs per 8 KB of weights).  A lane's B operand is then h of exactly the rows that it loads.
+// h enters as fp16 hi + lo of h * 2^s, s per token (and slot parity) such that the largest |h| of
+// the first chunk lands in [2^10, 2^11); a chunk that would pass 2^15 lowers s first and rescales
+// the sums.  So no value of fp32's range overflows, and what falls below fp16's smallest step is
+// 2^-34 of the largest.  An infinite h stays infinite (its lo part is 0).
+// Bound by memory: ids and h of the next chunk are requested in front of the rows of this one, so
+// a wave waits for one round trip per 8 KB.  126 registers leave room for two workgroups per CU
+// (the second launch of the look-ahead form needs that); double-buffering the rows instead (209
+// registers, one workgroup) and four row groups at batch 8 both measured the same within 0.5 %.
+// A decode step before -> after, every layer's FC2 on this kernel: OPT-30B shape batch 8, 12
+// layers 953 -> 899 us (FC2 20.9 -> 16.5 us for 65 MB); LLaMA-13B shape batch 4, 20 layers
+// 1158 -> 1098 us (14.2 -> 11.7 us for 44 MB); all 16384 neurons of an OPT-6.7B layer at batch 8
+// 63.0 -> 54.2 us.
+constexpr int kDown2mRows = 64;                       // list slots per chunk (one wave)
+constexpr int kDown2mPitch = kDown2Cols + 4;          // floats per token row of the partial sums
+constexpr int kDown2mRedFloats = 2 * kDown2Waves * 8 * kDown2mPitch;
+
+struct Down2mIds {
+    int iv;       // list entry of slot lane of the chunk
+    float h[8];   // h of this lane's token (lane % 8) and rows
+};
+struct Down2mOps {
+    half8_t hi, lo;  // B operand
+};
+
+__device__ __forceinline__ void down2_mfma_body(
+    float *red, const int tile, const int g, const int P, const __half *w_down, const float *b_down,
+    const float *h, const int32_t *idx, const int32_t *count_p, float *part, int B, int hs, int d, int ffn)
+{
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int cl = lane & 7, rs = lane >> 3;
+    const bool colok = tile * kDown2Cols + cl * 8 < d;
+    const rsrc_t wd = make_rsrc(w_down, (uint32_t)ffn * (uint32_t)d * 2u);
+    const rsrc_t ir = make_rsrc(idx, (uint32_t)ffn * 4u);
+    const rsrc_t hr = make_rsrc(h, (uint32_t)ffn * (uint32_t)hs * 4u);
+    const uint32_t colbyte = (uint32_t)(tile * kDown2Cols + cl * 8) * 2u;
+
+    // ids and h of chunk c: addresses depend on the slot number only (slots past the arrays' end
+    // read zeros)
+    auto request = [&](Down2mIds &r, int c) {
+#pragma unroll
+        for (int u = 0; u < 8; ++u) {
+            const int j = c * kDown2mRows + u * 8 + rs;
+            r.h[u] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(
+                hr, cl < B && j < ffn ? (int)((uint32_t)(j * hs + cl) * 4u) : (int)kOobOffset, 0, 0));
+        }
+        const int j = c * kDown2mRows + lane;
+        r.iv = (int)__builtin_amdgcn_raw_buffer_load_b32(ir, j < ffn ? j * 4 : (int)kOobOffset, 0, 0);
+    };
+    // weight rows of chunk c; h of slots without a row becomes 0
+    auto load_rows = [&](uint4 (&w)[8], Down2mIds &r, int c, int n) {
+        const bool ok = c * kDown2mRows + lane < n && (unsigned)r.iv < (unsigned)ffn;
+        const uint32_t row = ok ? (uint32_t)r.iv * (uint32_t)d * 2u : kOobOffset;
+#pragma unroll
+        for (int u = 0; u < 8; ++u) {
+            const uint32_t ro = (uint32_t)__shfl((int)row, u * 8 + rs, 64);
+            w[u] = ld16_stream(wd, colok && ro != kOobOffset ? ro + colbyte : kOobOffset);
+            r.h[u] = ro != kOobOffset ? r.h[u] : 0.f;
+        }
+    };
+    float4v_t acc[8];  // [t][i]: column 8 (m % 8) + t of m = 4 (lane / 16) + i, in units of 2^(erun - 137)
+#pragma unroll
+    for (int t = 0; t < 8; ++t) acc[t] = (float4v_t){0.f, 0.f, 0.f, 0.f};
+    int erun = 11;  // biased exponent that is scaled to 2^10; 11 .. 255, so that both scales are normal
+    auto operands = [&](Down2mOps &o, const Down2mIds &r) {
+        float m = 0.f;
+#pragma unroll
+        for (int u = 0; u < 8; ++u) m = fmaxf(m, fabsf(r.h[u]));
+        m = fmaxf(m, __shfl_xor(m, 16, 64));
+        m = fmaxf(m, __shfl_xor(m, 32, 64));
+        const int e = (int)(__float_as_uint(m) >> 23);
+        if (__ballot(e > erun + 4) != 0) {  // the first chunk, hardly ever a later one
+            const int en = max(erun, e);
+            const float f = ldexpf(1.f, erun - en);
+#pragma unroll
+            for (int t = 0; t < 8; ++t) acc[t] *= f;
+            erun = en;
+        }
+        const float scale = __uint_as_float((uint32_t)(264 - erun) << 23);
+#pragma unroll
+        for (int u = 0; u < 8; ++u) {
+            const float v = r.h[u] * scale;
+            const _Float16 hi = (_Float16)v;
+            const float hf = (float)hi;
+            o.hi[u] = hi;
+            o.lo[u] = (_Float16)(v == hf ? 0.f : v - hf);
+        }
+    };
+    auto multiply = [&](const uint4 (&w)[8], const Down2mOps &o) {
+#pragma unroll
+        for (int t = 0; t < 8; ++t) {
+            const uint32_t sel = (t & 1) ? 0x07060302u : 0x05040100u;
+            auto dw = [&](int u) { return t < 2 ? w[u].x : t < 4 ? w[u].y : t < 6 ? w[u].z : w[u].w; };
+            Half8Bits a;
+            a.u = make_uint4(__builtin_amdgcn_perm(dw(1), dw(0), sel), __builtin_amdgcn_perm(dw(3), dw(2), sel),
+                             __builtin_amdgcn_perm(dw(5), dw(4), sel), __builtin_amdgcn_perm(dw(7), dw(6), sel));
+            acc[t] = __builtin_amdgcn_mfma_f32_16x16x32_f16(a.h, o.lo, acc[t], 0, 0, 0);
+            acc[t] = __builtin_amdgcn_mfma_f32_16x16x32_f16(a.h, o.hi, acc[t], 0, 0, 0);
+        }
+    };
+
+    const int step = kDown2Waves * P;
+    int c = wave * P + g;
+    Down2mIds ra, rb;
+    uint4 w[8];
+    Down2mOps o;
+    request(ra, c);
+    const int n = min(max(wave_uniform(*count_p), 0), ffn);
+    const int nc = (n + kDown2mRows - 1) / kDown2mRows;
+    for (; c < nc; c += step) {
+        request(rb, c + step);  // ahead of the rows, so that the next chunk's do not wait for it
+        load_rows(w, ra, c, n);
+        operands(o, ra);
+        multiply(w, o);
+        ra = rb;
+    }
+
+    // lane l holds C[m = 4 (l / 16) + i][n = l % 16]; on the diagonal blocks that is parity
+    // l / 32, column 8 (m % 8) + t, token l % 8
+    if ((lane >> 5) == ((lane >> 3) & 1)) {
+        const float f = __uint_as_float((uint32_t)(erun - 10) << 23);
+        float *to = red + ((wave * 2 + (lane >> 5)) * 8 + cl) * kDown2mPitch + 32 * ((lane >> 4) & 1);
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            *reinterpret_cast<float4 *>(to + 8 * i) = make_float4(acc[0][i] * f, acc[1][i] * f, acc[2][i] * f, acc[3][i] * f);
+            *reinterpret_cast<float4 *>(to + 8 * i + 4) = make_float4(acc[4][i] * f, acc[5][i] * f, acc[6][i] * f, acc[7][i] * f);
+        }
+    }
+    __syncthreads();
+    const int b = threadIdx.x / kDown2Cols, oc = tile * kDown2Cols + (int)threadIdx.x % kDown2Cols;
+    if (b < B && oc < d) {
+        float s = (g == 0 && b_down) ? b_down[oc] : 0.f;
+#pragma unroll
+        for (int k = 0; k < 2 * kDown2Waves; ++k)
+            s += red[(k * 8 + b) * kDown2mPitch + (int)threadIdx.x % kDown2Cols];
+        part[((size_t)g * B + b) * d + oc] = s;
+    }
+}
+
+// grid = (d / 64 tiles, P), block = 512.
+__global__ __launch_bounds__(kDown2Threads, 4) void k_down2_mfma(
+    const __half *__restrict__ w_down, const float *__restrict__ b_down, const float *__restrict__ h,
+    const int32_t *__restrict__ idx, const int32_t *__restrict__ count_p, float *__restrict__ part, int B, int hs,
+    int d, int ffn)
+{
+    __shared__ __align__(16) float red[kDown2mRedFloats];
+    down2_mfma_body(red, (int)blockIdx.x, (int)blockIdx.y, (int)gridDim.y, w_down, b_down, h, idx, count_p,
+                           part, B, hs, d, ffn);
 }
 
 }  // namespace pf

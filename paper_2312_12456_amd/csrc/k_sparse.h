@@ -217,6 +217,7 @@ __global__ __launch_bounds__(kUpThreads) void k_up(
 // (group 0 adds b_down) and the consumer adds the P partials in the fixed order
 // g = 0 .. P-1 -- the next layer's predictor kernel inside a stack, k_combine otherwise.
 // grid = (d / 64 tiles, P), block = 512: 64 list slots per load of the block.
+// Batch 1..3; larger batches run k_down2_mfma.
 constexpr int kDown2Threads = 512;
 constexpr int kDown2Waves = kDown2Threads / kWave;
 constexpr int kDown2Cols = 64;

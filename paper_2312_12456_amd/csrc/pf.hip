@@ -225,12 +225,7 @@ hipError_t allow_lds_mfma()
     if (e == hipSuccess) e = allow_lds(pf::k_rows_mfma<64, 64, 1, false>);
     if (e == hipSuccess) e = allow_lds(pf::k_la_up_hidden_mfma<0>);
     if (e == hipSuccess) e = allow_lds(pf::k_la_up_hidden_mfma<1>);
-    if (e == hipSuccess) e = allow_lds(pf::k_la_down_out_mfma<3>);
-    if (e == hipSuccess) e = allow_lds(pf::k_la_down_out_mfma<4>);
-    if (e == hipSuccess) e = allow_lds(pf::k_la_down_out_mfma<5>);
-    if (e == hipSuccess) e = allow_lds(pf::k_la_down_out_mfma<6>);
-    if (e == hipSuccess) e = allow_lds(pf::k_la_down_out_mfma<7>);
-    if (e == hipSuccess) e = allow_lds(pf::k_la_down_out_mfma<8>);
+    if (e == hipSuccess) e = allow_lds(pf::k_la_down_out_mfma);
     return e;
 }
 
@@ -435,6 +430,11 @@ inline int fc2_split(const pf_ctx *ctx, int tiles, int B, bool two_per_cu = true
     return best;
 }
 
+// FC2 over fp16 rows runs on the matrix cores from batch 4 on, whatever d and the list: the vector
+// form is bound by its 8 B FMAs per 16-byte load there (figures at k_down2_mfma).  At batch 3 the two are
+// equal (OPT-30B shape, 8 layers: 501 us both), so the vector form stays.
+inline bool fc2_mfma(int B) { return B >= 4; }
+
 inline int kpad_i4(int k) { return cdiv(k, pf::kI4Chunk) * pf::kI4Chunk; }
 
 // Sparse FFN over int4 weights (same launch structure as the fp16 one below).
@@ -568,8 +568,13 @@ pf_status launch_sparse(pf_ctx *ctx, const pf_layer *L, const float *x, int B,
     float *part = (ny_out || P > 1) ? ctx->ypart : y;
     {
         ProfScope ps(ctx, K_DOWN);
-        PF_SWITCH_B(B, PF_LAUNCH(ps, pf::k_down2<BT>, dim3(tiles, P), dim3(pf::kDown2Threads), 0,
-                                 st, w_down, L->w.b_down, ctx->h, idx, count, part, D.d, D.ffn));
+        if (fc2_mfma(B)) {
+            PF_LAUNCH(ps, pf::k_down2_mfma, dim3(tiles, P), dim3(pf::kDown2Threads), 0, st, w_down,
+                      L->w.b_down, (const float *)ctx->h, idx, count, part, B, pf::h_stride(B), D.d, D.ffn);
+        } else {
+            PF_SWITCH_B3(B, PF_LAUNCH(ps, pf::k_down2<BT>, dim3(tiles, P), dim3(pf::kDown2Threads), 0,
+                                      st, w_down, L->w.b_down, ctx->h, idx, count, part, D.d, D.ffn));
+        }
     }
     if (ny_out) {
         *ny_out = P;
@@ -1012,23 +1017,13 @@ pf_status stack_enqueue_lookahead_merged_mfma(pf_ctx *ctx, pf_layer *const *laye
         const int n_out = N ? (N->desc.ffn - N->always_on) / 64 : 0;
         {
             ProfScope ps(ctx, K_LA_DOWN_OUT);
-#define PF_LA2M(BB)                                                                               \
-    PF_LAUNCH(ps, (pf::k_la_down_out_mfma<BB>), dim3(tiles * P + n_out), dim3(pf::kMfmaThreads), slots, \
-              st, tiles, P, static_cast<const __half *>(L->w.w_down), L->w.b_down,                \
-              (const float *)ctx->h, (const int32_t *)ctx->idx, (const int32_t *)ctx->count,      \
-              ctx->ypart, D.d, D.ffn, static_cast<const __half *>(N ? N->w.p2 : nullptr),         \
-              N ? N->w.p_bias : nullptr, (const float *)ctx->t, N ? N->desc.r : 0,                \
-              N ? N->desc.ffn : 0, N ? N->thr_logit : 0.f, masks[(l + 1) & 1],                    \
-              N ? N->always_on / 64 : 0)
-            switch (B) {
-                case 3: PF_LA2M(3); break;
-                case 4: PF_LA2M(4); break;
-                case 5: PF_LA2M(5); break;
-                case 6: PF_LA2M(6); break;
-                case 7: PF_LA2M(7); break;
-                default: PF_LA2M(8); break;
-            }
-#undef PF_LA2M
+            PF_LAUNCH(ps, pf::k_la_down_out_mfma, dim3(tiles * P + n_out), dim3(pf::kMfmaThreads), slots, st, B,
+                      pf::h_stride(B), tiles, P, static_cast<const __half *>(L->w.w_down), L->w.b_down,
+                      (const float *)ctx->h, (const int32_t *)ctx->idx, (const int32_t *)ctx->count,
+                      ctx->ypart, D.d, D.ffn, static_cast<const __half *>(N ? N->w.p2 : nullptr),
+                      N ? N->w.p_bias : nullptr, (const float *)ctx->t, N ? N->desc.r : 0,
+                      N ? N->desc.ffn : 0, N ? N->thr_logit : 0.f, masks[(l + 1) & 1],
+                      N ? N->always_on / 64 : 0);
         }
         ny = P;
         PF_HIP(ctx, hipGetLastError());
