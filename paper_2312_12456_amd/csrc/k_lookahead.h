@@ -95,7 +95,7 @@ static_assert(kMfmaThreads == kDown2Threads, "all roles of these launches use 51
 // layer's 64 KB of slots).
 template <int ACT>
 __global__ __launch_bounds__(kMfmaThreads) void k_la_up_hidden_mfma(
-    int n_hid, const __half *__restrict__ p1, float *__restrict__ t, int r,
+    int n_hid, const __half *__restrict__ p1, __half *__restrict__ t_split, int r,
     const __half *__restrict__ w_up, const __half *__restrict__ w_gate,
     const float *__restrict__ b_up, const void *__restrict__ xs, int B,
     const uint64_t *__restrict__ mask_words, int32_t *__restrict__ idx_out,
@@ -111,8 +111,8 @@ __global__ __launch_bounds__(kMfmaThreads) void k_la_up_hidden_mfma(
         up_mfma_body<ACT, true, true>(dyn_lds64, wave_tot, irow, brow, bid, n_up, w_up, w_gate, b_up, xs, B,
                                       nullptr, nullptr, mask_words, idx_out, count_out, h, hs, d, ffn, up_floor);
     } else {
-        rows_mfma_body<8, 512, 0, true>(dyn_lds64, logit_s, bid - n_up, p1, xs, B, d, r, nullptr, 0.f, t, nullptr,
-                                        0);
+        rows_mfma_body<8, 512, 0, true>(dyn_lds64, logit_s, bid - n_up, p1, xs, B, d, r, nullptr, 0.f, nullptr,
+                                        nullptr, 0, t_split);
     }
 }
 
@@ -124,7 +124,7 @@ __global__ __launch_bounds__(kMfmaThreads, 4) void k_la_down_out_mfma(
     int B, int hs, int tiles, int P, const __half *__restrict__ w_down, const float *__restrict__ b_down,
     const float *__restrict__ h, const int32_t *__restrict__ idx, const int32_t *__restrict__ count_p,
     float *__restrict__ part, int d, int ffn, const __half *__restrict__ p2,
-    const float *__restrict__ p_bias, const float *__restrict__ t, int r, int ffn_next, float thr_logit,
+    const float *__restrict__ p_bias, const __half *__restrict__ t_split, int r, int ffn_next, float thr_logit,
     uint64_t *__restrict__ mask_next, int first_word)
 {
     extern __shared__ uint64_t dyn_lds64[];
@@ -136,8 +136,8 @@ __global__ __launch_bounds__(kMfmaThreads, 4) void k_la_down_out_mfma(
         down2_mfma_body(reinterpret_cast<float *>(dyn_lds64), bid % tiles, bid / tiles, P, w_down, b_down,
                         h, idx, count_p, part, B, hs, d, ffn);
     } else {
-        rows_mfma_body<64, 64, 1, false>(dyn_lds64, logit_s, bid - n_fc2, p2, t, B, r, ffn_next, p_bias, thr_logit,
-                                         nullptr, mask_next, first_word);
+        rows_mfma_body<64, 64, 1, true>(dyn_lds64, logit_s, bid - n_fc2, p2, t_split, B, r, ffn_next, p_bias,
+                                        thr_logit, nullptr, mask_next, first_word);
     }
 }
 

@@ -217,7 +217,7 @@ __global__ __launch_bounds__(kUpThreads) void k_up(
 // (group 0 adds b_down) and the consumer adds the P partials in the fixed order
 // g = 0 .. P-1 -- the next layer's predictor kernel inside a stack, k_combine otherwise.
 // grid = (d / 64 tiles, P), block = 512: 64 list slots per load of the block.
-// Batch 1..3; larger batches run k_down2_mfma.
+// Batches of 4 and more whose FC1 runs on the matrix cores take k_down2_mfma instead.
 constexpr int kDown2Threads = 512;
 constexpr int kDown2Waves = kDown2Threads / kWave;
 constexpr int kDown2Cols = 64;
@@ -355,9 +355,21 @@ __global__ __launch_bounds__(256) void k_combine(const float *__restrict__ part,
 // Stack glue: x_next[b] = sign(b, .) * (x[b] + y[b]) * sqrt(d) / ||x[b] + y[b]||_2.  grid = B.
 constexpr int kGlueThreads = 1024;
 
-// Four consecutive values as fp16 hi + lo at element `at` of the hi plane and of the lo plane
-// `plane` halfs behind it.
-__device__ __forceinline__ void store_split4(__half *xs, size_t plane, size_t at, const float4 &o)
+// The activations of a batch as fp16 hi + lo halves in the order in which the matrix-core kernels
+// take them: element c of token b's hi half is at half split_at(hs, b, c), hs = h_stride(B), its
+// lo half hs * 8 halfs further.  8 consecutive elements of one token's half are contiguous, then
+// come the other tokens' hi and lo halves of the same 8 elements: the operand of one matrix
+// instruction (32 elements, all tokens, both halves) is one run of 128 hs bytes.  (Planes of
+// [B][d] halfs cost the consumers two loads per step of 64-byte pieces from every token's row:
+// at the OPT-30B shape, batch 8, the hidden layer's 192 workgroups touched four times as many
+// lines for activations as for weights.)
+__device__ __forceinline__ size_t split_at(int hs, int b, int c)
+{
+    return (size_t)(c >> 3) * (size_t)(16 * hs) + (size_t)(b * 8 + (c & 7));
+}
+
+// Elements c .. c + 3 (c % 4 == 0) of token b.
+__device__ __forceinline__ void store_split4(__half *xs, int hs, int b, int c, const float4 &o)
 {
     _Float16 hi[4], lo[4];
     split_f32(o.x, hi[0], lo[0]);
@@ -365,9 +377,9 @@ __device__ __forceinline__ void store_split4(__half *xs, size_t plane, size_t at
     split_f32(o.z, hi[2], lo[2]);
     split_f32(o.w, hi[3], lo[3]);
     typedef _Float16 half4_t __attribute__((ext_vector_type(4)));
-    *reinterpret_cast<half4_t *>(reinterpret_cast<_Float16 *>(xs) + at) = (half4_t){hi[0], hi[1], hi[2], hi[3]};
-    *reinterpret_cast<half4_t *>(reinterpret_cast<_Float16 *>(xs) + plane + at) =
-        (half4_t){lo[0], lo[1], lo[2], lo[3]};
+    _Float16 *to = reinterpret_cast<_Float16 *>(xs) + split_at(hs, b, c);
+    *reinterpret_cast<half4_t *>(to) = (half4_t){hi[0], hi[1], hi[2], hi[3]};
+    *reinterpret_cast<half4_t *>(to + hs * 8) = (half4_t){lo[0], lo[1], lo[2], lo[3]};
 }
 
 // x_next may alias x: every element is read and written by the same thread.
@@ -377,8 +389,7 @@ __device__ __forceinline__ void store_split4(__half *xs, size_t plane, size_t at
 // reduction, then the stores.
 constexpr int kGlueMaxD = kGlueThreads * 4 * 4;
 
-// xs_next (may be null): the same values split into fp16 hi and lo planes, [B][d] each, lo
-// plane B * d halfs behind the hi plane (the operand format of the matrix-core kernels).
+// xs_next (may be null; d % 8 == 0): the same values as fp16 hi and lo halves, see split_at.
 __global__ __launch_bounds__(kGlueThreads) void k_glue(const float *x, const float *__restrict__ y,
                                                        int ny, float *x_next, int d, __half *xs_next)
 {
@@ -421,7 +432,7 @@ __global__ __launch_bounds__(kGlueThreads) void k_glue(const float *x, const flo
         if (e < d) {
             const float4 o = make_float4(v[i].x * scale, v[i].y * scale, v[i].z * scale, v[i].w * scale);
             *reinterpret_cast<float4 *>(x_next + (size_t)b * d + e) = o;
-            if (xs_next != nullptr) store_split4(xs_next, (size_t)gridDim.x * d, (size_t)b * d + e, o);
+            if (xs_next != nullptr) store_split4(xs_next, h_stride((int)gridDim.x), b, e, o);
         }
     }
 }
@@ -458,18 +469,20 @@ __global__ __launch_bounds__(kGlueThreads) void k_glue_long(const float *x, cons
         if (xs_next != nullptr) {
             _Float16 hi, lo;
             split_f32(o, hi, lo);
-            reinterpret_cast<_Float16 *>(xs_next)[(size_t)b * d + c] = hi;
-            reinterpret_cast<_Float16 *>(xs_next)[(size_t)gridDim.x * d + (size_t)b * d + c] = lo;
+            const int hs = h_stride((int)gridDim.x);
+            _Float16 *to = reinterpret_cast<_Float16 *>(xs_next) + split_at(hs, b, c);
+            to[0] = hi;
+            to[hs * 8] = lo;
         }
     }
 }
 
-// The split planes of a caller's activations x[n] (n = B * d, a multiple of 4): xs[0 .. n) hi,
-// xs[n .. 2n) lo.  grid = ceil(n / 1024), block = 256.
-__global__ __launch_bounds__(256) void k_split(const float *__restrict__ x, __half *__restrict__ xs, int n)
+// The split halves of a caller's activations x[B][d] (d % 8 == 0).  grid = ceil(B * d / 1024),
+// block = 256.
+__global__ __launch_bounds__(256) void k_split(const float *__restrict__ x, __half *__restrict__ xs, int B, int d)
 {
     const int e = ((int)blockIdx.x * 256 + (int)threadIdx.x) * 4;
-    if (e < n) store_split4(xs, (size_t)n, (size_t)e, *reinterpret_cast<const float4 *>(x + e));
+    if (e < B * d) store_split4(xs, h_stride(B), e / d, e % d, *reinterpret_cast<const float4 *>(x + e));
 }
 
 }  // namespace pf

@@ -49,9 +49,10 @@ struct pf_ctx {
     int up_grid_cap_i4 = 512;
     int mfma_grid = 0;              // PF_OPT_MFMA_GRID: blocks of k_up_mfma (0 = from the CU count)
     // The hidden layer goes to the matrix cores only above this B * d: below it the vector kernel
-    // with the glue fused in beats MFMA + a glue kernel of its own (measured: +1..3 % on the
-    // stack at 4 x 4096 and 4 x 5120, -9 % and worse from 8 x 4096 on).
-    int hidden_mfma_min_elems = 20480;
+    // with the glue fused in beats MFMA + a glue kernel of its own.  Measured, vector / matrix, us
+    // a stack step: 4 x 768 215 / 240, 8 x 768 249 / 247, 5 x 2048 303 / 302, 3 x 5120 600 / 600,
+    // 4 x 4096 463 / 441, 4 x 5120 1098 / 1058.
+    int hidden_mfma_min_elems = 15360;
     int lds_budget = kLdsDefault;  // dynamic LDS a kernel of this context may request
     int down_split = 0;            // PF_OPT_DOWN_SPLIT: row groups of FC2 (0 = from the CU count)
     int mfma_min_batch = 4;        // FC1 goes to the matrix cores from this batch size on
@@ -76,12 +77,16 @@ struct pf_ctx {
     float *h = nullptr;              // [max_ffn][h_stride(batch)] FC1 outputs, by list slot
     float *ypart = nullptr;          // [4][max_batch][max_d] FC2 output as partial sums
     float *xbuf[2] = {nullptr, nullptr};  // [max_batch][max_d] layer inputs inside pf_stack_step
-    // fp16 hi + lo planes of the activations the matrix-core kernels read ([2][B][d] halfs each;
-    // two buffers, used in turn); split_src = the fp32 array whose split xsplit[split_cur] holds,
+    // fp16 hi + lo halves of the activations the matrix-core kernels read (pf::split_at; 2 d
+    // h_stride(B) halfs each; two buffers, used in turn); split_src = the fp32 array whose split xsplit[split_cur] holds,
     // valid within one entry-point call only (reset by check_batch)
     __half *xsplit[2] = {nullptr, nullptr};
     const float *split_src = nullptr;
     int split_cur = 0;
+    // the predictor's hidden vector in the same form, beside t: which of the two the last enqueued
+    // hidden layer wrote
+    __half *tsplit = nullptr;
+    bool t_split = false;
     bool split_off = false;  // set while kernels are enqueued on a second stream
     hipStream_t capture_stream = nullptr;
     // look-ahead mode: predictors on a stream of their own, masks double-buffered
@@ -223,6 +228,7 @@ hipError_t allow_lds_mfma()
     if (e == hipSuccess) e = allow_lds(pf::k_rows_mfma<8, 512, 0, true>);
     if (e == hipSuccess) e = allow_lds(pf::k_rows_mfma<8, 512, 0, false>);
     if (e == hipSuccess) e = allow_lds(pf::k_rows_mfma<64, 64, 1, false>);
+    if (e == hipSuccess) e = allow_lds(pf::k_rows_mfma<64, 64, 1, true>);
     if (e == hipSuccess) e = allow_lds(pf::k_la_up_hidden_mfma<0>);
     if (e == hipSuccess) e = allow_lds(pf::k_la_up_hidden_mfma<1>);
     if (e == hipSuccess) e = allow_lds(pf::k_la_down_out_mfma);
@@ -245,7 +251,7 @@ hipError_t allow_lds_all()
 
 pf_status check_batch(pf_ctx *ctx, const pf_layer *layer, const void *x, int B)
 {
-    if (ctx) ctx->split_src = nullptr;  // no split planes carry over from an earlier call
+    if (ctx) ctx->split_src = nullptr;  // no split halves carry over from an earlier call
     if (!ctx) return PF_EINVAL;
     if (!layer || !x) return fail(ctx, PF_EINVAL, "null layer or input");
     if (layer->ctx != ctx) return fail(ctx, PF_EINVAL, "layer belongs to another context");
@@ -321,22 +327,25 @@ pf_status launch_hidden(pf_ctx *ctx, const pf_layer *L, const float *x, const fl
             if (s != PF_OK) return s;
             x = x_new;
         }
-        const __half *xs = nullptr;  // the activations as fp16 hi + lo planes where possible
+        const __half *xs = nullptr;  // the activations as fp16 hi + lo halves where possible
         pf_status s = ensure_split(ctx, x, B, D.d, st, &xs);
         if (s != PF_OK) return s;
+        ctx->t_split = ctx->tsplit != nullptr && pred_mfma(ctx, D, D.r, B);
+        __half *ts = ctx->t_split ? ctx->tsplit : nullptr;
         ProfScope ps(ctx, K_PRED_HIDDEN);
         if (xs)
             PF_LAUNCH(ps, (pf::k_rows_mfma<8, 512, 0, true>), dim3(cdiv(D.r, 8)), dim3(pf::kMfmaThreads),
                       (size_t)pf::kMfmaWaves * pf::kRowsMfmaSlotBytes, st, p1, (const void *)xs, B, D.d, D.r,
-                      (const float *)nullptr, 0.f, ctx->t, (uint64_t *)nullptr, 0, skip);
+                      (const float *)nullptr, 0.f, ctx->t, (uint64_t *)nullptr, 0, skip, ts);
         else
             PF_LAUNCH(ps, (pf::k_rows_mfma<8, 512, 0, false>), dim3(cdiv(D.r, 8)), dim3(pf::kMfmaThreads),
                       (size_t)pf::kMfmaWaves * pf::kRowsMfmaSlotBytes, st, p1, (const void *)x, B, D.d, D.r,
-                      (const float *)nullptr, 0.f, ctx->t, (uint64_t *)nullptr, 0, skip);
+                      (const float *)nullptr, 0.f, ctx->t, (uint64_t *)nullptr, 0, skip, ts);
         PF_HIP(ctx, hipGetLastError());
         return PF_OK;
     }
     // hidden layer, in batch tiles that fit LDS
+    ctx->t_split = false;
     if (glue_y && ctx->split_src == x_new) ctx->split_src = nullptr;  // x_new is rewritten as fp32 only
     const int tile = batch_tile(ctx, D.d, B, 1024);
     for (int b0 = 0; b0 < B; b0 += tile) {
@@ -381,9 +390,16 @@ pf_status launch_predict(pf_ctx *ctx, const pf_layer *L, const float *x, const f
     const __half *p2 = static_cast<const __half *>(L->w.p2);
     if (pred_mfma(ctx, D, D.r, B)) {
         ProfScope ps(ctx, K_PRED_OUT);
-        PF_LAUNCH(ps, (pf::k_rows_mfma<64, 64, 1, false>), dim3(pred_out_words(L)), dim3(pf::kMfmaThreads),
-                  (size_t)pf::kMfmaWaves * pf::kRowsMfmaSlotBytes, st, p2, (const void *)ctx->t, B, D.r,
-                  D.ffn, L->w.p_bias, L->thr_logit, scores, mask_words, L->always_on / 64, skip);
+        // the hidden vector as split halves where the matrix-core hidden layer has just left it so
+#define PF_OUTM(XSV, V)                                                                             \
+    PF_LAUNCH(ps, (pf::k_rows_mfma<64, 64, 1, XSV>), dim3(pred_out_words(L)), dim3(pf::kMfmaThreads), \
+              (size_t)pf::kMfmaWaves * pf::kRowsMfmaSlotBytes, st, p2, (const void *)(V), B, D.r, D.ffn, \
+              L->w.p_bias, L->thr_logit, scores, mask_words, L->always_on / 64, skip, (__half *)nullptr)
+        if (ctx->t_split)
+            PF_OUTM(true, ctx->tsplit);
+        else
+            PF_OUTM(false, ctx->t);
+#undef PF_OUTM
         PF_HIP(ctx, hipGetLastError());
         return PF_OK;
     }
@@ -429,11 +445,6 @@ inline int fc2_split(const pf_ctx *ctx, int tiles, int B, bool two_per_cu = true
     }
     return best;
 }
-
-// FC2 over fp16 rows runs on the matrix cores from batch 4 on, whatever d and the list: the vector
-// form is bound by its 8 B FMAs per 16-byte load there (figures at k_down2_mfma).  At batch 3 the two are
-// equal (OPT-30B shape, 8 layers: 501 us both), so the vector form stays.
-inline bool fc2_mfma(int B) { return B >= 4; }
 
 inline int kpad_i4(int k) { return cdiv(k, pf::kI4Chunk) * pf::kI4Chunk; }
 
@@ -526,7 +537,7 @@ pf_status launch_sparse(pf_ctx *ctx, const pf_layer *L, const float *x, int B,
         // 7 us, so two rounds of smaller blocks lose more than their longer chunks gain
         const int grid = ctx->mfma_grid > 0 ? ctx->mfma_grid : ctx->num_cu;
         ProfScope ps(ctx, K_UP_MFMA);
-        // the activations as split planes where this call has them already (the glue kernel or
+        // the activations as split halves where this call has them already (the glue kernel or
         // the matrix-core hidden layer in front made them; only calls that predict get there),
         // else as fp32 values
         const __half *xs = from_mask ? split_of(ctx, x) : nullptr;
@@ -568,11 +579,17 @@ pf_status launch_sparse(pf_ctx *ctx, const pf_layer *L, const float *x, int B,
     float *part = (ny_out || P > 1) ? ctx->ypart : y;
     {
         ProfScope ps(ctx, K_DOWN);
-        if (fc2_mfma(B)) {
+        // On the matrix cores from batch 4 on where FC1 is: the vector form is bound by its 8 B FMAs
+        // per 16-byte load there (figures at k_down2_mfma); at batch 3 the two are equal (OPT-30B
+        // shape, 8 layers: 501 us both).  Behind the vector FC1 (d no multiple of 32) it would be 7 %
+        // faster (2056 x 5568 gated, batch 5: 33.2 -> 30.7 us) but the layer's error against 64 bits
+        // 6 % larger; behind the matrix-core FC1 the layer's error is below that of the vector FC2
+        // with both of FC1's halves summed in one tile.
+        if (mfma && B >= 4) {
             PF_LAUNCH(ps, pf::k_down2_mfma, dim3(tiles, P), dim3(pf::kDown2Threads), 0, st, w_down,
                       L->w.b_down, (const float *)ctx->h, idx, count, part, B, pf::h_stride(B), D.d, D.ffn);
         } else {
-            PF_SWITCH_B3(B, PF_LAUNCH(ps, pf::k_down2<BT>, dim3(tiles, P), dim3(pf::kDown2Threads), 0,
+            PF_SWITCH_B(B, PF_LAUNCH(ps, pf::k_down2<BT>, dim3(tiles, P), dim3(pf::kDown2Threads), 0,
                                       st, w_down, L->w.b_down, ctx->h, idx, count, part, D.d, D.ffn));
         }
     }
@@ -668,12 +685,12 @@ pf_status launch_layer_fused(pf_ctx *ctx, const pf_layer *L, const float *x, con
     return PF_OK;
 }
 
-// split: also leave x_next as fp16 hi + lo planes for the matrix-core kernels (split_of(x_next)).
+// split: also leave x_next as fp16 hi + lo halves for the matrix-core kernels (split_of(x_next)).
 pf_status launch_glue(pf_ctx *ctx, const float *x, const float *y, int ny, int d, int B,
                       float *x_next, hipStream_t st, bool split)
 {
     __half *xs = nullptr;
-    if (split && d % 4 == 0 && ctx->xsplit[0] != nullptr && !ctx->split_off) {
+    if (split && d % 8 == 0 && ctx->xsplit[0] != nullptr && !ctx->split_off) {
         ctx->split_cur ^= 1;
         xs = ctx->xsplit[ctx->split_cur];
         ctx->split_src = x_next;
@@ -691,26 +708,25 @@ pf_status launch_glue(pf_ctx *ctx, const float *x, const float *y, int ny, int d
     return PF_OK;
 }
 
-// The split planes of x if this call has produced them already, else null.
+// The split halves of x if this call has produced them already, else null.
 const __half *split_of(const pf_ctx *ctx, const float *x)
 {
     return (x != nullptr && !ctx->split_off && ctx->split_src == x) ? ctx->xsplit[ctx->split_cur] : nullptr;
 }
 
-// The split planes of x, produced by a small kernel if this call has not made them yet.
+// The split halves of x, produced by a small kernel if this call has not made them yet.
 pf_status ensure_split(pf_ctx *ctx, const float *x, int B, int d, hipStream_t st, const __half **xs)
 {
     *xs = split_of(ctx, x);
     if (*xs) return PF_OK;
     // no planes: a context without the buffers, an odd shape, or kernels being enqueued on a
     // second stream (the planes' bookkeeping follows one stream); the caller reads fp32 then
-    if (!ctx->xsplit[0] || (B * d) % 4 != 0 || ctx->split_off) return PF_OK;
+    if (!ctx->xsplit[0] || d % 8 != 0 || ctx->split_off) return PF_OK;
     ctx->split_cur ^= 1;
     __half *dst = ctx->xsplit[ctx->split_cur];
-    const int n = B * d;
     {
         ProfScope ps(ctx, K_GLUE);
-        PF_LAUNCH(ps, pf::k_split, dim3(cdiv(n, 1024)), dim3(256), 0, st, x, dst, n);
+        PF_LAUNCH(ps, pf::k_split, dim3(cdiv(B * d, 1024)), dim3(256), 0, st, x, dst, B, d);
     }
     PF_HIP(ctx, hipGetLastError());
     ctx->split_src = x;
@@ -777,7 +793,7 @@ pf_status stack_enqueue_lookahead(pf_ctx *ctx, pf_layer *const *layers, int n_la
     PF_HIP(ctx, hipEventRecord(fork, st));
     PF_HIP(ctx, hipStreamWaitEvent(side, fork, 0));
     auto predict_on_side = [&](int l, const float *seen) -> pf_status {
-        ctx->split_off = true;  // the split planes' bookkeeping follows the main stream only
+        ctx->split_off = true;  // the split halves' bookkeeping follows the main stream only
         pf_status s = launch_predict(ctx, layers[l], seen, nullptr, 0, nullptr, B, nullptr, masks[l & 1], side);
         ctx->split_off = false;
         if (s != PF_OK) return s;
@@ -982,7 +998,7 @@ pf_status stack_enqueue_lookahead_merged_mfma(pf_ctx *ctx, pf_layer *const *laye
             if (s != PF_OK) return s;
             cur = xn;
         }
-        const __half *xs = nullptr;  // both roles of the first launch read the split planes
+        const __half *xs = nullptr;  // both roles of the first launch read the split halves
         s = ensure_split(ctx, cur, B, d, st, &xs);
         if (s != PF_OK) return s;
         const int n_hid = N ? cdiv(N->desc.r, 8) : 0;
@@ -994,7 +1010,7 @@ pf_status stack_enqueue_lookahead_merged_mfma(pf_ctx *ctx, pf_layer *const *laye
             ProfScope ps(ctx, K_LA_UP_HIDDEN);
 #define PF_LA1M(ACT)                                                                                   \
     PF_LAUNCH(ps, (pf::k_la_up_hidden_mfma<ACT>), dim3(n_up + n_hid), dim3(pf::kMfmaThreads), lds1, st, \
-              n_hid, static_cast<const __half *>(N ? N->w.p1 : nullptr), ctx->t, N ? N->desc.r : 0,    \
+              n_hid, static_cast<const __half *>(N ? N->w.p1 : nullptr), ctx->tsplit, N ? N->desc.r : 0, \
               static_cast<const __half *>(L->w.w_up), static_cast<const __half *>(L->w.w_gate),        \
               L->w.b_up, (const void *)xs, B, (const uint64_t *)masks[l & 1], ctx->idx, ctx->count,    \
               ctx->h,                                                                                  \
@@ -1021,7 +1037,7 @@ pf_status stack_enqueue_lookahead_merged_mfma(pf_ctx *ctx, pf_layer *const *laye
                       pf::h_stride(B), tiles, P, static_cast<const __half *>(L->w.w_down), L->w.b_down,
                       (const float *)ctx->h, (const int32_t *)ctx->idx, (const int32_t *)ctx->count,
                       ctx->ypart, D.d, D.ffn, static_cast<const __half *>(N ? N->w.p2 : nullptr),
-                      N ? N->w.p_bias : nullptr, (const float *)ctx->t, N ? N->desc.r : 0,
+                      N ? N->w.p_bias : nullptr, (const __half *)ctx->tsplit, N ? N->desc.r : 0,
                       N ? N->desc.ffn : 0, N ? N->thr_logit : 0.f, masks[(l + 1) & 1],
                       N ? N->always_on / 64 : 0);
         }
@@ -1416,8 +1432,9 @@ pf_status pf_ctx_create(pf_ctx **out, int device, int max_d, int max_ffn, int ma
         PF_ALLOC(ctx->ypart, (size_t)pf::kDown2MaxSplit * max_batch * max_d * sizeof(float));
         PF_ALLOC(ctx->xbuf[0], (size_t)max_batch * max_d * sizeof(float));
         PF_ALLOC(ctx->xbuf[1], (size_t)max_batch * max_d * sizeof(float));
-        PF_ALLOC(ctx->xsplit[0], (size_t)2 * max_batch * max_d * sizeof(__half));
-        PF_ALLOC(ctx->xsplit[1], (size_t)2 * max_batch * max_d * sizeof(__half));
+        PF_ALLOC(ctx->tsplit, (size_t)2 * pf::h_stride(max_batch) * max_r * sizeof(__half));
+        PF_ALLOC(ctx->xsplit[0], (size_t)2 * pf::h_stride(max_batch) * max_d * sizeof(__half));
+        PF_ALLOC(ctx->xsplit[1], (size_t)2 * pf::h_stride(max_batch) * max_d * sizeof(__half));
 #undef PF_ALLOC
         e = hipMemset(ctx->count, 0, 64);
         if (e == hipSuccess) {
@@ -1455,6 +1472,7 @@ void pf_ctx_destroy(pf_ctx *ctx)
     (void)hipFree(ctx->count_all);
     (void)hipFree(ctx->h);
     (void)hipFree(ctx->ypart);
+    (void)hipFree(ctx->tsplit);
     (void)hipFree(ctx->xsplit[0]);
     (void)hipFree(ctx->xsplit[1]);
     (void)hipFree(ctx->xbuf[0]);

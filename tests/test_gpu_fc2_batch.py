@@ -49,7 +49,7 @@ def _case(pf, d, ffn, n, B, spread, up_scale=1.0, b_up=None):
 
 @pytest.mark.parametrize("B", [4, 5, 8])
 @pytest.mark.parametrize("n", [0, 1, 63, 64, 65, 511, 512, 1000, 1024])
-@pytest.mark.parametrize("d", [72, 2056])
+@pytest.mark.parametrize("d", [96, 2056, 2080])
 def test_fc2_batch_list_lengths(pf, d, n, B):
     y, ref, tol = _case(pf, d, 1024, n, B, spread=0.0)
     assert bool(((y - ref).abs() <= tol).all()), float(((y - ref).abs() - tol).max())
