@@ -1432,9 +1432,12 @@ pf_status pf_ctx_create(pf_ctx **out, int device, int max_d, int max_ffn, int ma
         PF_ALLOC(ctx->ypart, (size_t)pf::kDown2MaxSplit * max_batch * max_d * sizeof(float));
         PF_ALLOC(ctx->xbuf[0], (size_t)max_batch * max_d * sizeof(float));
         PF_ALLOC(ctx->xbuf[1], (size_t)max_batch * max_d * sizeof(float));
-        PF_ALLOC(ctx->tsplit, (size_t)2 * pf::h_stride(max_batch) * max_r * sizeof(__half));
         PF_ALLOC(ctx->xsplit[0], (size_t)2 * pf::h_stride(max_batch) * max_d * sizeof(__half));
         PF_ALLOC(ctx->xsplit[1], (size_t)2 * pf::h_stride(max_batch) * max_d * sizeof(__half));
+        // only batches of 3 and more pass the hidden vector on in this form
+        if (max_batch >= 3) {
+            PF_ALLOC(ctx->tsplit, (size_t)2 * pf::h_stride(max_batch) * max_r * sizeof(__half));
+        }
 #undef PF_ALLOC
         e = hipMemset(ctx->count, 0, 64);
         if (e == hipSuccess) {
