@@ -638,25 +638,27 @@ __global__ __launch_bounds__(kMfmaThreads) void k_rows_mfma(
 // B's columns carry h of the even slots' rows for tokens 0..7, then of the odd slots' rows.
 // The two off-diagonal 8 x 8 blocks of the result are not used (the matrix cores have room:
 // 16 MFMAs per 8 KB of weights).  A lane's B operand is then h of exactly the rows that it loads.
-// h enters as fp16 hi + lo of h * 2^s, s per token (and slot parity) such that the largest |h| of
-// the first chunk lands in [2^10, 2^11); a chunk that would pass 2^15 lowers s first and rescales
-// the sums.  So no value of fp32's range overflows, and what falls below fp16's smallest step is
-// 2^-34 of the largest.  An infinite h stays infinite (its lo part is 0).
-// Precision: the matrix cores cut a sum at the last bit of its largest term, towards minus
-// infinity.  Error against 64 bits of the whole FFN with every neuron listed (2-norm, 1e-7;
-// OPT-6.7B shape batch 8 / LLaMA-13B batch 4 / OPT-30B batch 8), FC1 as it is now: both halves
-// summed on in the running tile 1.90 / 2.71 / 2.66; lo, then hi on top of it, from zero per chunk
-// 2.47 / 2.95 / 3.12; hi and lo each from zero per chunk and added by vector additions 1.69 /
-// 2.55 / 2.17 -- taken.  The vector form: 1.49 / 2.38 / 1.82, and 1.77 / 3.19 / 2.21 while FC1
-// still summed its two halves in one tile.
+// h enters with all of its 24 bits, as three fp16 parts of 8 bits each: h * 2^s = p1 + p2 / 2^8 +
+// p3 / 2^16, s per chunk, token and slot parity such that the largest |h| lands in [2^14, 2^15).
+// The split is exact down to 2^-31 of that largest value; a chunk with a smaller h other than zero
+// is added up without the matrix cores (plain_chunk), so that a column in which the large values
+// have no weight is as accurate as any other.
+// Precision: a matrix instruction takes its products in four groups of 8 (k = 0..7, 8..15, ...; all
+// of this measured on the device).  In each group it cuts the products, towards zero, and the sum so
+// far, towards minus infinity, at 2^-26 of (a bound on) the largest product, adds, and rounds to
+// nearest.  So each part's products are summed from zero and added to the running sum by ordinary
+// operations, 8-bit parts leave the products 5 bits before the cut reaches them, and the rows of odd
+// slots enter negated, which turns the bias of the second cut round (without: -1 to -6 * 10^-8 of the
+// rms).  Error of this kernel alone against 64 bits (2-norm, 1e-8; list length x d, batch 4), in
+// front the vector form, behind it two 11-bit halves under a running scale with the 16 partial sums
+// added in a chain: 1500 x 2048 9.3 / 10.4 -> 8.0; 2600 x 4096 9.6 / 11.4 -> 8.3; 5000 x 5120 10.6 /
+// 11.6 -> 8.7; 28672 x 7168 15.9 / 13.4 -> 10.8.
 // Bound by memory: ids and h of the next chunk are requested in front of the rows of this one, so
-// a wave waits for one round trip per 8 KB.  128 registers leave room for two workgroups per CU
-// (the second launch of the look-ahead form needs that); double-buffering the rows instead (209
-// registers, one workgroup) and four row groups at batch 8 both measured the same within 0.5 %.
-// A decode step before -> after, every layer's FC2 on this kernel: OPT-30B shape batch 8, 12
-// layers 953 -> 899 us (FC2 20.9 -> 16.5 us for 65 MB); LLaMA-13B shape batch 4, 20 layers
-// 1158 -> 1098 us (14.2 -> 11.7 us for 44 MB); all 16384 neurons of an OPT-6.7B layer at batch 8
-// 63.0 -> 54.2 us.
+// a wave waits for one round trip per 8 KB.  124 registers leave room for two workgroups per CU
+// (the second launch of the look-ahead form needs that).
+// Vector form -> this one, us: OPT-30B shape batch 8 (65 MB) 21.9 -> 17.4, LLaMA-13B shape batch 4
+// (44 MB) 14.8 -> 12.3, all 16384 neurons of an OPT-6.7B layer at batch 4 (134 MB) 35.3 -> 25.7.
+// (The two-half form: 17.3, 11.9, 26.2.)
 constexpr int kDown2mRows = 64;                       // list slots per chunk (one wave)
 constexpr int kDown2mPitch = kDown2Cols + 4;          // floats per token row of the partial sums
 constexpr int kDown2mRedFloats = 2 * kDown2Waves * 8 * kDown2mPitch;
@@ -666,8 +668,24 @@ struct Down2mIds {
     float h[8];   // h of this lane's token (lane % 8) and rows
 };
 struct Down2mOps {
-    half8_t hi, lo;  // B operand
+    half8_t p1, p2, p3;  // B operand: h * scale = p1 + p2 / 2^8 + p3 / 2^16
 };
+
+// a, b cut to their 8 leading bits as fp16 halves (subnormal halves to multiples of 2^-21).
+__device__ __forceinline__ uint32_t top8_halves(float a, float b)
+{
+    const auto h = __builtin_amdgcn_cvt_pkrtz(a, b);
+    uint32_t u;
+    __builtin_memcpy(&u, &h, 4);
+    return u & 0xFFF8FFF8u;
+}
+__device__ __forceinline__ float half_f32(uint32_t pair, int i)
+{
+    const uint16_t u = (uint16_t)(pair >> (16 * i));
+    _Float16 h;
+    __builtin_memcpy(&h, &u, 2);
+    return (float)h;
+}
 
 __device__ __forceinline__ void down2_mfma_body(
     float *red, const int tile, const int g, const int P, const __half *w_down, const float *b_down,
@@ -693,7 +711,8 @@ __device__ __forceinline__ void down2_mfma_body(
         const int j = c * kDown2mRows + lane;
         r.iv = (int)__builtin_amdgcn_raw_buffer_load_b32(ir, j < ffn ? j * 4 : (int)kOobOffset, 0, 0);
     };
-    // weight rows of chunk c; h of slots without a row becomes 0
+    // weight rows of chunk c; h of slots without a row becomes 0.  Returns the byte offset of the row
+    // of slot lane.
     auto load_rows = [&](uint4 (&w)[8], Down2mIds &r, int c, int n) {
         const bool ok = c * kDown2mRows + lane < n && (unsigned)r.iv < (unsigned)ffn;
         const uint32_t row = ok ? (uint32_t)r.iv * (uint32_t)d * 2u : kOobOffset;
@@ -703,36 +722,49 @@ __device__ __forceinline__ void down2_mfma_body(
             w[u] = ld16_stream(wd, colok && ro != kOobOffset ? ro + colbyte : kOobOffset);
             r.h[u] = ro != kOobOffset ? r.h[u] : 0.f;
         }
+        return row;
     };
-    float4v_t acc[8];  // [t][i]: column 8 (m % 8) + t of m = 4 (lane / 16) + i, in units of 2^(erun - 137)
+    float4v_t acc[8];  // [t][i]: column 8 (m % 8) + t of m = 4 (lane / 16) + i
 #pragma unroll
     for (int t = 0; t < 8; ++t) acc[t] = (float4v_t){0.f, 0.f, 0.f, 0.f};
-    int erun = 11;  // biased exponent that is scaled to 2^10; 11 .. 255, so that both scales are normal
-    auto operands = [&](Down2mOps &o, const Down2mIds &r) {
+    // The operand of a chunk, and in f what takes its products back to h's units.  True where the
+    // three parts do not hold every bit of every h.
+    auto operands = [&](Down2mOps &o, float &f, const Down2mIds &r) {
         float m = 0.f;
-#pragma unroll
-        for (int u = 0; u < 8; ++u) m = fmaxf(m, fabsf(r.h[u]));
-        m = fmaxf(m, __shfl_xor(m, 16, 64));
-        m = fmaxf(m, __shfl_xor(m, 32, 64));
-        const int e = (int)(__float_as_uint(m) >> 23);
-        if (__ballot(e > erun + 4) != 0) {  // the first chunk, hardly ever a later one
-            const int en = max(erun, e);
-            const float f = ldexpf(1.f, erun - en);
-#pragma unroll
-            for (int t = 0; t < 8; ++t) acc[t] *= f;
-            erun = en;
-        }
-        const float scale = __uint_as_float((uint32_t)(264 - erun) << 23);
+        uint32_t least = ~0u;  // of 2 bits(|h|) - 1: zero counts as the largest
 #pragma unroll
         for (int u = 0; u < 8; ++u) {
-            const float v = r.h[u] * scale;
-            const _Float16 hi = (_Float16)v;
-            const float hf = (float)hi;
-            o.hi[u] = hi;
-            o.lo[u] = (_Float16)(v == hf ? 0.f : v - hf);
+            m = fmaxf(m, fabsf(r.h[u]));
+            least = min(least, (__float_as_uint(r.h[u]) << 1) - 1u);
         }
+        m = fmaxf(m, __shfl_xor(m, 16, 64));
+        m = fmaxf(m, __shfl_xor(m, 32, 64));
+        const int e = max((int)(__float_as_uint(m) >> 23), 15);  // 15 .. 255: both scales are normal
+        const uint32_t sign = (uint32_t)(lane & 8) << 28;        // odd row slots
+        const float scale = __uint_as_float(sign | (uint32_t)(268 - e) << 23);
+        f = __uint_as_float(sign | (uint32_t)(e - 14) << 23);
+        uint32_t p1[4], p2[4], p3[4];
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {  // every step but the last conversion is exact
+            const float v0 = r.h[2 * k] * scale, v1 = r.h[2 * k + 1] * scale;
+            p1[k] = top8_halves(v0, v1);
+            const float a0 = fmaf(-256.f, half_f32(p1[k], 0), 256.f * v0);
+            const float a1 = fmaf(-256.f, half_f32(p1[k], 1), 256.f * v1);
+            p2[k] = top8_halves(a0, a1);
+            const auto h = __builtin_amdgcn_cvt_pkrtz(fmaf(-256.f, half_f32(p2[k], 0), 256.f * a0),
+                                                      fmaf(-256.f, half_f32(p2[k], 1), 256.f * a1));
+            __builtin_memcpy(&p3[k], &h, 4);
+        }
+        Half8Bits b;
+        b.u = make_uint4(p1[0], p1[1], p1[2], p1[3]);
+        o.p1 = b.h;
+        b.u = make_uint4(p2[0], p2[1], p2[2], p2[3]);
+        o.p2 = b.h;
+        b.u = make_uint4(p3[0], p3[1], p3[2], p3[3]);
+        o.p3 = b.h;
+        return least < (uint32_t)max(e - 31, 0) << 24;  // some 0 < |h * scale| < 2^-17
     };
-    auto multiply = [&](const uint4 (&w)[8], const Down2mOps &o) {
+    auto multiply = [&](const uint4 (&w)[8], const Down2mOps &o, float f) {
 #pragma unroll
         for (int t = 0; t < 8; ++t) {
             const uint32_t sel = (t & 1) ? 0x07060302u : 0x05040100u;
@@ -740,14 +772,45 @@ __device__ __forceinline__ void down2_mfma_body(
             Half8Bits a;
             a.u = make_uint4(__builtin_amdgcn_perm(dw(1), dw(0), sel), __builtin_amdgcn_perm(dw(3), dw(2), sel),
                              __builtin_amdgcn_perm(dw(5), dw(4), sel), __builtin_amdgcn_perm(dw(7), dw(6), sel));
-            // each half's products from zero, then into the running sum by ordinary additions: the
-            // matrix cores cut what they add at the last bit of the largest term (see above)
+            // each part's products from zero, then into the running sum by ordinary operations
             const float4v_t z = {0.f, 0.f, 0.f, 0.f};
-            const float4v_t lo = __builtin_amdgcn_mfma_f32_16x16x32_f16(a.h, o.lo, z, 0, 0, 0);
-            const float4v_t hi = __builtin_amdgcn_mfma_f32_16x16x32_f16(a.h, o.hi, z, 0, 0, 0);
-            acc[t] += hi + lo;
+            const float4v_t s3 = __builtin_amdgcn_mfma_f32_16x16x32_f16(a.h, o.p3, z, 0, 0, 0);
+            const float4v_t s2 = __builtin_amdgcn_mfma_f32_16x16x32_f16(a.h, o.p2, z, 0, 0, 0);
+            const float4v_t s1 = __builtin_amdgcn_mfma_f32_16x16x32_f16(a.h, o.p1, z, 0, 0, 0);
+#pragma unroll
+            for (int i = 0; i < 4; ++i)
+                acc[t][i] = fmaf(fmaf(fmaf(s3[i], 0x1p-8f, s2[i]), 0x1p-8f, s1[i]), f, acc[t][i]);
             __builtin_amdgcn_sched_barrier(0);  // bounds the registers of the chunk's sums
         }
+    };
+    // Lane l holds C[m = 4 (l / 16) + i][n = l % 16]; on the diagonal blocks that is row-slot parity
+    // l / 32, columns 32 (l / 16 % 2) + 8 i + t, token l % 8.
+    const int par = lane >> 5, chalf = (lane >> 4) & 1;
+    const bool mine = par == ((lane >> 3) & 1);
+    // A chunk without the matrix cores: the same sums in fp32, one row after the other.
+    auto plain_chunk = [&](uint32_t row, int c) {
+        float4v_t sum[8];
+#pragma unroll
+        for (int t = 0; t < 8; ++t) sum[t] = (float4v_t){0.f, 0.f, 0.f, 0.f};
+#pragma unroll 1
+        for (int s = 0; s < kDown2mRows / 2; ++s) {
+            const int slot = 2 * s + par, j = c * kDown2mRows + slot;
+            const uint32_t ro = (uint32_t)__shfl((int)row, slot, 64);
+            const bool ok = mine && cl < B && ro != kOobOffset;  // then j < ffn
+            const float hv = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(
+                hr, ok ? (int)((uint32_t)(j * hs + cl) * 4u) : (int)kOobOffset, 0, 0));
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                const int col = tile * kDown2Cols + 32 * chalf + 8 * i;
+                const uint4 q = ld16_cached(wd, ok && col < d ? ro + (uint32_t)col * 2u : kOobOffset);
+                const uint32_t qd[4] = {q.x, q.y, q.z, q.w};
+#pragma unroll
+                for (int t = 0; t < 8; ++t)
+                    sum[t][i] = fmaf(hv, (t & 1) ? h_hi(qd[t / 2]) : h_lo(qd[t / 2]), sum[t][i]);
+            }
+        }
+#pragma unroll
+        for (int t = 0; t < 8; ++t) acc[t] += sum[t];
     };
 
     const int step = kDown2Waves * P;
@@ -755,36 +818,41 @@ __device__ __forceinline__ void down2_mfma_body(
     Down2mIds ra, rb;
     uint4 w[8];
     Down2mOps o;
+    float f;
     request(ra, c);
     const int n = min(max(wave_uniform(*count_p), 0), ffn);
     const int nc = (n + kDown2mRows - 1) / kDown2mRows;
     for (; c < nc; c += step) {
         request(rb, c + step);  // ahead of the rows, so that the next chunk's do not wait for it
-        load_rows(w, ra, c, n);
-        operands(o, ra);
-        multiply(w, o);
+        const uint32_t row = load_rows(w, ra, c, n);
+        if (__ballot(operands(o, f, ra)) == 0)
+            multiply(w, o, f);
+        else
+            plain_chunk(row, c);
         ra = rb;
     }
 
-    // lane l holds C[m = 4 (l / 16) + i][n = l % 16]; on the diagonal blocks that is parity
-    // l / 32, column 8 (m % 8) + t, token l % 8
-    if ((lane >> 5) == ((lane >> 3) & 1)) {
-        const float f = __uint_as_float((uint32_t)(erun - 10) << 23);
-        float *to = red + ((wave * 2 + (lane >> 5)) * 8 + cl) * kDown2mPitch + 32 * ((lane >> 4) & 1);
+    if (mine) {
+        float *to = red + ((wave * 2 + par) * 8 + cl) * kDown2mPitch + 32 * chalf;
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
-            *reinterpret_cast<float4 *>(to + 8 * i) = make_float4(acc[0][i] * f, acc[1][i] * f, acc[2][i] * f, acc[3][i] * f);
-            *reinterpret_cast<float4 *>(to + 8 * i + 4) = make_float4(acc[4][i] * f, acc[5][i] * f, acc[6][i] * f, acc[7][i] * f);
+            *reinterpret_cast<float4 *>(to + 8 * i) = make_float4(acc[0][i], acc[1][i], acc[2][i], acc[3][i]);
+            *reinterpret_cast<float4 *>(to + 8 * i + 4) = make_float4(acc[4][i], acc[5][i], acc[6][i], acc[7][i]);
         }
     }
     __syncthreads();
     const int b = threadIdx.x / kDown2Cols, oc = tile * kDown2Cols + (int)threadIdx.x % kDown2Cols;
     if (b < B && oc < d) {
-        float s = (g == 0 && b_down) ? b_down[oc] : 0.f;
+        // the 16 sums in pairs: a chain of 16 additions would be the largest error of the kernel
+        float s[2 * kDown2Waves];
 #pragma unroll
         for (int k = 0; k < 2 * kDown2Waves; ++k)
-            s += red[(k * 8 + b) * kDown2mPitch + (int)threadIdx.x % kDown2Cols];
-        part[((size_t)g * B + b) * d + oc] = s;
+            s[k] = red[(k * 8 + b) * kDown2mPitch + (int)threadIdx.x % kDown2Cols];
+#pragma unroll
+        for (int o2 = kDown2Waves; o2 >= 1; o2 /= 2)
+#pragma unroll
+            for (int k = 0; k < o2; ++k) s[k] += s[k + o2];
+        part[((size_t)g * B + b) * d + oc] = (g == 0 && b_down) ? b_down[oc] + s[0] : s[0];
     }
 }
 

@@ -580,11 +580,9 @@ pf_status launch_sparse(pf_ctx *ctx, const pf_layer *L, const float *x, int B,
     {
         ProfScope ps(ctx, K_DOWN);
         // On the matrix cores from batch 4 on where FC1 is: the vector form is bound by its 8 B FMAs
-        // per 16-byte load there (figures at k_down2_mfma); at batch 3 the two are equal (OPT-30B
-        // shape, 8 layers: 501 us both).  Behind the vector FC1 (d no multiple of 32) it would be 7 %
-        // faster (2056 x 5568 gated, batch 5: 33.2 -> 30.7 us) but the layer's error against 64 bits
-        // 6 % larger; behind the matrix-core FC1 the layer's error is below that of the vector FC2
-        // with both of FC1's halves summed in one tile.
+        // per 16-byte load there (figures, error against 64 bits among them, at k_down2_mfma); at
+        // batch 3 the two are equal (OPT-30B shape, 8 layers: 501 us both).  Widths that are no
+        // multiple of 32 run the vector FC1 and the vector FC2 behind it.
         if (mfma && B >= 4) {
             PF_LAUNCH(ps, pf::k_down2_mfma, dim3(tiles, P), dim3(pf::kDown2Threads), 0, st, w_down,
                       L->w.b_down, (const float *)ctx->h, idx, count, part, B, pf::h_stride(B), D.d, D.ffn);
