@@ -627,7 +627,7 @@ __global__ __launch_bounds__(kMfmaThreads) void k_rows_mfma(
 // ---------------------------------------------------------------------------------------
 // FC2 over the listed neurons for a batch, on the matrix cores: y^T[column][token] =
 // sum over slots of W_down^T[row][column] * h[slot][token].  The vector form (down2_body) issues
-// 8 B + 12 vector instructions per 16-byte load; here it is about 30 whatever the batch.
+// 8 B + 12 vector instructions per 16-byte load; here it is about 35 whatever the batch.
 // Tiling of down2_body: a workgroup owns 64 columns (a whole 128-byte line per row) and every
 // P-th chunk of 64 list slots of each wave, and a lane loads 16 bytes (columns 8 cl .. 8 cl + 7,
 // cl = lane % 8) of each of 8 rows.  No LDS and no cross-lane step stands between these loads and
@@ -637,7 +637,7 @@ __global__ __launch_bounds__(kMfmaThreads) void k_rows_mfma(
 // m < 8 belong to even row slots and need tokens n < 8, rows m >= 8 to odd ones and n >= 8, so
 // B's columns carry h of the even slots' rows for tokens 0..7, then of the odd slots' rows.
 // The two off-diagonal 8 x 8 blocks of the result are not used (the matrix cores have room:
-// 16 MFMAs per 8 KB of weights).  A lane's B operand is then h of exactly the rows that it loads.
+// 24 MFMAs per 8 KB of weights).  A lane's B operand is then h of exactly the rows that it loads.
 // h enters with all of its 24 bits, as three fp16 parts of 8 bits each: h * 2^s = p1 + p2 / 2^8 +
 // p3 / 2^16, s per chunk, token and slot parity such that the largest |h| lands in [2^14, 2^15).
 // The split is exact down to 2^-31 of that largest value; a chunk with a smaller h other than zero
@@ -830,6 +830,23 @@ __device__ __forceinline__ void down2_mfma_body(
         else
             plain_chunk(row, c);
         ra = rb;
+    }
+    // An infinite weight or h may have met a part of h that is zero, or another of the other sign:
+    // sums that are not finite are formed once more without the parts.
+    float nan = 0.f;
+#pragma unroll
+    for (int t = 0; t < 8; ++t)
+#pragma unroll
+        for (int i = 0; i < 4; ++i) nan = fmaf(acc[t][i], 0.f, nan);
+    if (__ballot(mine && nan != 0.f) != 0) {
+#pragma unroll
+        for (int t = 0; t < 8; ++t) acc[t] = (float4v_t){0.f, 0.f, 0.f, 0.f};
+#pragma unroll 1
+        for (c = wave * P + g; c < nc; c += step) {
+            const int j = c * kDown2mRows + lane;
+            const int i = (int)__builtin_amdgcn_raw_buffer_load_b32(ir, j < n ? j * 4 : (int)kOobOffset, 0, 0);
+            plain_chunk(j < n && (unsigned)i < (unsigned)ffn ? (uint32_t)i * (uint32_t)d * 2u : kOobOffset, c);
+        }
     }
 
     if (mine) {

@@ -181,6 +181,33 @@ def test_fc2_alone_no_less_accurate_than_the_vector_form(pf, n, B):
     assert err[False] <= 1.02 * err[True], err
 
 
+@pytest.mark.gpu
+@pytest.mark.parametrize("B", [4, 8])
+def test_fc2_alone_infinite_weights_and_outputs(pf, B):
+    """An infinite weight or FC1 output makes a column infinite, with the sign of the product; where
+    the other factor is zero, or infinities of both signs meet, it is NaN.  The rest stays finite."""
+    inf = float("inf")
+    w_up, b_up, w_down, h = _fc2_inputs("relu", 1500, 96, B)
+    w_down[7, 3], w_down[700, 20], w_down[1400, 20], w_down[900, 50] = inf, -inf, inf, inf
+    w_up[7], b_up[7] = 1.0, 2.0 ** -9           # 8 bits: the last part of h is zero
+    w_up[700], b_up[700] = 1.0, 0.3
+    w_up[1400], b_up[1400] = 1.0, 0.3
+    w_up[900, ::2], w_up[900, 1::2] = -9.0, 2.0  # off for every other token
+    h = torch.relu(w_up.float() + b_up[:, None]).double()
+    for case in range(2):
+        if case:
+            b_up[33] = inf
+            w_down[33, 5] = 0.0
+            h = torch.relu(w_up.float() + b_up[:, None]).double()
+        ref = torch.stack([(h[:, b:b + 1] * w_down.double()).sum(0) for b in range(B)])
+        fin = torch.isfinite(ref)
+        for split in (0, 1):
+            y = _fc2_run(pf, w_up, b_up, w_down, B, split).double()
+            assert torch.equal(torch.isnan(y), torch.isnan(ref))
+            assert torch.equal(y[torch.isinf(ref)], ref[torch.isinf(ref)])
+            torch.testing.assert_close(y[fin], ref[fin], rtol=0, atol=40 * 2.0 ** -24 * float(h.sum()))
+
+
 @pytest.mark.parametrize("kind,n,d,B", [("relu", 1, 32, 4), ("relu", 65, 96, 5), ("relu", 4100, 2080, 8),
                                         ("tiny", 1500, 96, 4), ("grow", 1500, 96, 4), ("gap30", 1500, 96, 4),
                                         ("gap45", 1500, 96, 7), ("gap100", 1500, 96, 7)])
