@@ -49,10 +49,8 @@ struct pf_ctx {
     int up_grid_cap_i4 = 512;
     int mfma_grid = 0;              // PF_OPT_MFMA_GRID: blocks of k_up_mfma (0 = from the CU count)
     // The hidden layer goes to the matrix cores only above this B * d: below it the vector kernel
-    // with the glue fused in beats MFMA + a glue kernel of its own.  Measured, vector / matrix, us
-    // a stack step: 4 x 768 215 / 240, 8 x 768 249 / 247, 5 x 2048 303 / 302, 3 x 5120 600 / 600,
-    // 4 x 4096 463 / 441, 4 x 5120 1098 / 1058.
-    int hidden_mfma_min_elems = 15360;
+    // with the glue fused in beats MFMA + a glue kernel of its own.
+    int hidden_mfma_min_elems = 20480;
     int lds_budget = kLdsDefault;  // dynamic LDS a kernel of this context may request
     int down_split = 0;            // PF_OPT_DOWN_SPLIT: row groups of FC2 (0 = from the CU count)
     int mfma_min_batch = 4;        // FC1 goes to the matrix cores from this batch size on
