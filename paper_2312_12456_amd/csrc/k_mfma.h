@@ -9,11 +9,11 @@
 // and B[same 8 k][col l%16]; it receives C[rows 4*(l/16) .. +3][col l%16].
 // Activations stay fp32-exact: x is split into fp16 hi + fp16 lo (x = hi + lo to 2^-21).  Where the
 // halves come ready-made (XS), both ride in one MFMA, as a batch has at most 8 tokens: with hs =
-// h_stride(B) column b multiplies the hi half of token b and column hs + b its lo half, and the two
-// columns are added when the waves' tiles are.  Where a kernel splits fp32 activations itself, each
-// step issues two MFMAs into two tiles (lanes of both column ranges splitting the same values
-// measured 2 - 6 % slower: OPT-6.7B shape with every neuron listed, batch 8, 54.4 -> 57.7 us), which
-// are added at the same point: both forms give the same bits.
+// h_stride(B) column b multiplies the hi half of token b and column hs + b its lo half.  Where a
+// kernel splits fp32 activations itself, each step issues two MFMAs into two tiles (lanes of both
+// column ranges splitting the same values measured 2 - 6 % slower: OPT-6.7B shape with every neuron
+// listed, batch 8, 54.4 -> 57.7 us).  Each wave's two sums are added first, then the waves' (see
+// put_tile): both forms give the same bits.
 //
 // Weights do not go to the registers in operand order: a load in which each quarter-wave
 // touches 16 different rows costs the memory pipeline 16 line look-ups for 256 bytes.
@@ -117,6 +117,24 @@ __device__ __forceinline__ void finish_x(const XRaw &r, half8_t &hi, half8_t &lo
             lo[e] = l;
         }
     }
+}
+
+// The waves' sums over a tile meet in LDS, [16 rows][16 columns] each.  XS: the lo half of column b is
+// column hs + b, and the two are added as they are read.  Else the lo halves are a tile of their own
+// and are added first, which keeps the traffic that of one tile and gives the same bits.
+template <bool XS>
+__device__ __forceinline__ void put_tile(float *ct, float4v_t hi, const float4v_t &lo, int kg, int row16, int hs)
+{
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+        if (!XS) hi[e] += lo[e];
+        if (XS || row16 < hs) ct[(kg * 4 + e) * 16 + row16] = hi[e];
+    }
+}
+template <bool XS>
+__device__ __forceinline__ float get_tile(const float *ct, int e, int el)  // el: of the lo column
+{
+    return XS ? ct[e] + ct[el] : ct[e];
 }
 
 // Put chunk `c` (KC = 4096 / R elements) of the R rows of a pass in flight towards `slot`.  One
@@ -277,35 +295,22 @@ __device__ __forceinline__ void up_mfma_passes(const UpMfmaArgs &a)
             for (int t = 0; t < T; ++t) a.brow[16 * t + row16] = bpre[t];
         }
 #pragma unroll
-        for (int t = 0; t < T; ++t)
-#pragma unroll
-            for (int e = 0; e < 4; ++e) {
-                const int at = (t * 2) * 256 + (kg * 4 + e) * 16 + row16;
-                if (XS || row16 < a.hs) {
-                    ctile[at] = cu[t][e];
-                    if (GATED) ctile[at + 256] = cg[t][e];
-                }
-                if (!XS && row16 < a.hs) {
-                    ctile[at + a.hs] = lu[t][e];
-                    if (GATED) ctile[at + 256 + a.hs] = lg[t][e];
-                }
-            }
+        for (int t = 0; t < T; ++t) {
+            put_tile<XS>(ctile + (t * 2) * 256, cu[t], lu[t], kg, row16, a.hs);
+            if (GATED) put_tile<XS>(ctile + (t * 2 + 1) * 256, cg[t], lg[t], kg, row16, a.hs);
+        }
         __syncthreads();
         if ((int)threadIdx.x < T * 256) {
             const int t = threadIdx.x >> 8, e = threadIdx.x & 255;
             const int row = 16 * t + (e >> 4), colb = e & 15;
             const int el = (e & ~15) + ((colb + a.hs) & 15);  // the same token's lo column
-            float su = 0.f, sg = 0.f, su_lo = 0.f, sg_lo = 0.f;
+            float su = 0.f, sg = 0.f;
 #pragma unroll
             for (int wv = 0; wv < kMfmaWaves; ++wv) {
                 const float *ct = reinterpret_cast<const float *>(a.slots + (size_t)wv * NM * kMfmaSlotBytes);
-                su += ct[(t * 2) * 256 + e];
-                su_lo += ct[(t * 2) * 256 + el];
-                if (GATED) sg += ct[(t * 2 + 1) * 256 + e];
-                if (GATED) sg_lo += ct[(t * 2 + 1) * 256 + el];
+                su += get_tile<XS>(ct + (t * 2) * 256, e, el);
+                if (GATED) sg += get_tile<XS>(ct + (t * 2 + 1) * 256, e, el);
             }
-            su += su_lo;
-            sg += sg_lo;
             const int i = a.irow[row];
             const int j = j0 + row;
             const float bias = a.brow[row];  // fetched when the row was selected
@@ -548,13 +553,7 @@ __device__ __forceinline__ void rows_mfma_body(
     // this lane holds C[tile t][row 4*kg + e][col row16] of its chunks; the slot is free now
     float *ctile = reinterpret_cast<float *>(slot);
 #pragma unroll
-    for (int t = 0; t < T; ++t)
-#pragma unroll
-        for (int e = 0; e < 4; ++e) {
-            const int at = t * 256 + (kg * 4 + e) * 16 + row16;
-            if (XS || row16 < hs) ctile[at] = acc[t][e];
-            if (!XS && row16 < hs) ctile[at + hs] = acc_lo[t][e];
-        }
+    for (int t = 0; t < T; ++t) put_tile<XS>(ctile + t * 256, acc[t], acc_lo[t], kg, row16, hs);
     __syncthreads();
 #pragma unroll
     for (int i = 0; i < NE; ++i) {
@@ -562,14 +561,10 @@ __device__ __forceinline__ void rows_mfma_body(
         if (e >= T * 256) break;
         const int row = (e >> 8) * 16 + ((e >> 4) & 15), col = e & 15;
         const int el = (e & ~15) + ((col + hs) & 15);  // the same token's lo column
-        float sum = 0.f, sum_lo = 0.f;
+        float sum = 0.f;
 #pragma unroll
-        for (int wv = 0; wv < kMfmaWaves; ++wv) {
-            const float *ct = reinterpret_cast<const float *>(slots + (size_t)wv * kRowsMfmaSlotBytes);
-            sum += ct[e];
-            sum_lo += ct[el];
-        }
-        sum += sum_lo;
+        for (int wv = 0; wv < kMfmaWaves; ++wv)
+            sum += get_tile<XS>(reinterpret_cast<const float *>(slots + (size_t)wv * kRowsMfmaSlotBytes), e, el);
         if (EPI == 0) {
             if (col < B && row < R && row < nleft) {
                 const float o = fmaxf(sum, 0.f);

@@ -51,14 +51,24 @@ def test_noalloc_layer_step_twice_second_call_smaller(pf):
 
 def test_noalloc_on_matrix_cores_same_bits_from_fp32_operands(pf):
     """Batch 4 with rows of a multiple of 32 elements runs on the matrix cores.  pf_layer_step
-    hands FC1 and the hidden layer the activations as fp16 hi + lo planes written by a small
-    kernel in front; the entry point that allocates nothing has no buffer for the planes and
-    splits inside the kernels.  Both are the same arithmetic: the outputs are equal bit for bit."""
+    hands FC1 and the hidden layer the activations as fp16 hi + lo halves written by a small
+    kernel in front; the entry point that allocates nothing has no buffer for them and splits
+    inside the kernels.  Both are the same arithmetic: the outputs are equal bit for bit."""
     for act in (wl.ACT_RELU, wl.ACT_REGLU):
         cfg = small_cfg(d=6144, ffn=4160, r=256, rate=0.15, act=act)  # B * d above the hidden layer's matrix-core threshold
         y, y_ref = _both(pf, cfg, 74 + act, 4)
         assert np.abs(y_ref).max() > 0.1
         assert np.array_equal(y, y_ref)
+
+
+@pytest.mark.parametrize("act", [wl.ACT_RELU, wl.ACT_REGLU])
+@pytest.mark.parametrize("d,r,B", [(7168, 64, 3), (5184, 136, 4), (8192, 96, 4)])
+def test_noalloc_on_matrix_cores_same_bits_ragged(pf, d, r, B, act):
+    """The same with fewer tokens than columns kept for them, rows that end inside a chunk, and a
+    hidden vector that the output layer takes as fp32 values (r no multiple of 32)."""
+    y, y_ref = _both(pf, small_cfg(d=d, ffn=1344, r=r, rate=0.15, act=act), 81 + act, B)
+    assert np.abs(y_ref).max() > 0.1
+    assert np.array_equal(y, y_ref)
 
 
 def test_noalloc_rejects_sizes_beyond_its_limits(pf):
