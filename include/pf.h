@@ -88,12 +88,13 @@ typedef struct pf_plan pf_plan;
  * in fp32.  Small batches multiply fp32 activations with the widened weights on the vector
  * units.  From 4 tokens on -- from 3 where d > 4096 -- FC1 of fp16 layers and the predictor of all
  * layers run on the matrix cores (row lengths that are a multiple of 32; the predictor's hidden
- * layer only above B * d = 20480, see PF_OPT_HIDDEN_MFMA_MIN_ELEMS), where each fp32 activation
- * enters as the sum of two fp16 numbers (rounded value + residual, 22 bits kept for values of 0.25
- * and more, an absolute 2^-25 below); what enters there -- x, and the hidden vector in front of
- * the predictor's output layer -- must lie inside the fp16 range (|x| < 65504), which normalised
- * hidden states do by orders of magnitude.  FC2 of such batches takes FC1's outputs with all of
- * their bits and over all of fp32's range.
+ * layer only for larger B * d, see PF_OPT_HIDDEN_MFMA_MIN_ELEMS), where each fp32 activation enters
+ * as the sum of two fp16 numbers (rounded value + scaled residual: to 2^-24 of the value, or 2^-36
+ * where that is more).  What enters there from outside -- x of pf_predict, pf_sparse_ffn,
+ * pf_dense_ffn and the layer steps, the first x of a stack -- and the predictor's hidden vector must
+ * lie inside the fp16 range (|x| < 65504), which normalised hidden states do by orders of
+ * magnitude.  FC2 of such batches takes FC1's outputs with all of their bits and over all of
+ * fp32's range.
  *
  * Context: binds a device and owns scratch sized for the given maxima (hidden vector,
  * mask words, index list, FC1 outputs, FC2 partial sums).  `device` is a HIP ordinal.
@@ -257,7 +258,8 @@ pf_status pf_ctx_set_lookahead(pf_ctx *ctx, int distance);
  *   PF_OPT_MFMA_MIN_BATCH   batch size from which FC1 and the predictor run on the matrix
  *                           cores (default rule: 4, and 3 where d > 4096); 0 = default rule
  *   PF_OPT_HIDDEN_MFMA_MIN_ELEMS  the predictor's hidden layer joins them only above this
- *                           B * d (default 20480; every value >= 0 is taken as given)
+ *                           B * d (default 20480, and 15360 behind the glue of a stack of fp16
+ *                           layers; every value >= 0 is taken as given, for both)
  *   PF_OPT_UP_GRID          workgroups of the vector FC1 kernel (default 8 per CU; int4: 2)
  *   PF_OPT_MFMA_GRID        workgroups of the matrix-core FC1 kernel (default one per CU)
  *   PF_OPT_DOWN_SPLIT       row groups of FC2, 1 .. 4 (default CUs / column tiles, at most 4)

@@ -168,12 +168,14 @@ __device__ __forceinline__ uint4 ld16_cached(rsrc_t r, uint32_t byte_off)
     return make_uint4(v.x, v.y, v.z, v.w);
 }
 
-// fp32 -> fp16 hi (rounded) + fp16 lo (residual): v = hi + lo to 2^-21 |v|.  The matrix-core
-// kernels multiply fp16 weights by both halves, so activations stay fp32-exact.
+// fp32 -> fp16 hi (rounded) + fp16 lo (residual, times 2^11): v = hi + lo / 2^11 to 2^-24 |v|, or to
+// 2^-36 where that is more.  (With the residual as it is, its smallest step of 2^-24 cuts off bits of
+// every |v| below 1.)  The matrix-core kernels multiply fp16 weights by both halves.
+constexpr float kSplitLo = 0x1p-11f;  // what a sum over lo halves counts
 __device__ __forceinline__ void split_f32(float v, _Float16 &hi, _Float16 &lo)
 {
     hi = (_Float16)v;
-    lo = (_Float16)(v - (float)hi);
+    lo = (_Float16)((v - (float)hi) * (1.f / kSplitLo));
 }
 
 __device__ __forceinline__ int wave_uniform(int v) { return __builtin_amdgcn_readfirstlane(v); }

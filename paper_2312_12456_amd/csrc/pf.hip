@@ -49,8 +49,15 @@ struct pf_ctx {
     int up_grid_cap_i4 = 512;
     int mfma_grid = 0;              // PF_OPT_MFMA_GRID: blocks of k_up_mfma (0 = from the CU count)
     // The hidden layer goes to the matrix cores only above this B * d: below it the vector kernel
-    // with the glue fused in beats MFMA + a glue kernel of its own.
+    // with the glue fused in beats MFMA + a glue kernel of its own.  In front of a layer whose input
+    // the library forms itself (inside a stack: |x| <= sqrt(d)) and whose FC1 then finds it as split
+    // halves (fp16), the line is lower.  Measured there, vector / matrix, us a step of 10 layers, B x d
+    // (r): 4 x 2048 (256) 239 / 246, 5 x 2048 (512) 254 / 256, 3 x 5120 (1024) 425 / 415, 4 x 4096
+    // (256) 343 / 334, (2048) 510 / 462, 7 x 2560 (128) 317 / 273, 3 x 6144 (128) 418 / 413.  Other
+    // inputs keep fp32's range up to 20480: single layers gain nothing (4 x 4096: 32.6 us both) and
+    // int4 stacks nothing (4 x 4096, 12 layers: 545 / 549).
     int hidden_mfma_min_elems = 20480;
+    int hidden_mfma_min_elems_glue = 15360;
     int lds_budget = kLdsDefault;  // dynamic LDS a kernel of this context may request
     int down_split = 0;            // PF_OPT_DOWN_SPLIT: row groups of FC2 (0 = from the CU count)
     int mfma_min_batch = 4;        // FC1 goes to the matrix cores from this batch size on
@@ -318,7 +325,9 @@ pf_status launch_hidden(pf_ctx *ctx, const pf_layer *L, const float *x, const fl
     const pf_layer_desc &D = L->desc;
     if (!L->w.p1 || !L->w.p2) return fail(ctx, PF_EINVAL, "layer has no predictor weights");
     const __half *p1 = static_cast<const __half *>(L->w.p1);
-    if (pred_mfma(ctx, D, D.d, B) && (size_t)B * (size_t)D.d > (size_t)ctx->hidden_mfma_min_elems) {
+    const int min_elems =
+        glue_y && D.wtype == PF_W_FP16 ? ctx->hidden_mfma_min_elems_glue : ctx->hidden_mfma_min_elems;
+    if (pred_mfma(ctx, D, D.d, B) && (size_t)B * (size_t)D.d > (size_t)min_elems) {
         // a batch on the matrix cores; the glue, if any, as a kernel of its own in front
         if (glue_y) {
             pf_status s = launch_glue(ctx, x, glue_y, glue_ny, D.d, B, x_new, st, true);
@@ -1735,7 +1744,7 @@ pf_status pf_ctx_set_option(pf_ctx *ctx, int key, int value)
             return PF_OK;
         case PF_OPT_HIDDEN_MFMA_MIN_ELEMS:
             if (value < 0) break;
-            ctx->hidden_mfma_min_elems = value;
+            ctx->hidden_mfma_min_elems = ctx->hidden_mfma_min_elems_glue = value;
             return PF_OK;
         case PF_OPT_UP_GRID:
             if (value < 0 || value > 65535) break;
