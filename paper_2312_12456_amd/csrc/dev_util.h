@@ -175,7 +175,7 @@ constexpr float kSplitLo = 0x1p-11f;  // what a sum over lo halves counts
 __device__ __forceinline__ void split_f32(float v, _Float16 &hi, _Float16 &lo)
 {
     hi = (_Float16)v;
-    lo = (_Float16)((v - (float)hi) * (1.f / kSplitLo));
+    lo = (_Float16)fmaf((float)hi, -1.f / kSplitLo, v * (1.f / kSplitLo));  // exact up to the conversion
 }
 
 __device__ __forceinline__ int wave_uniform(int v) { return __builtin_amdgcn_readfirstlane(v); }
