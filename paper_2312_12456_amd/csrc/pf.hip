@@ -49,15 +49,18 @@ struct pf_ctx {
     int up_grid_cap_i4 = 512;
     int mfma_grid = 0;              // PF_OPT_MFMA_GRID: blocks of k_up_mfma (0 = from the CU count)
     // The hidden layer goes to the matrix cores only above this B * d: below it the vector kernel
-    // with the glue fused in beats MFMA + a glue kernel of its own.  In front of a layer whose input
-    // the library forms itself (inside a stack: |x| <= sqrt(d)) and whose FC1 then finds it as split
-    // halves (fp16), the line is lower.  Measured there, vector / matrix, us a step of 10 layers, B x d
-    // (r): 4 x 2048 (256) 239 / 246, 5 x 2048 (512) 254 / 256, 3 x 5120 (1024) 425 / 415, 4 x 4096
-    // (256) 343 / 334, (2048) 510 / 462, 7 x 2560 (128) 317 / 273, 3 x 6144 (128) 418 / 413.  Other
-    // inputs keep fp32's range up to 20480: single layers gain nothing (4 x 4096: 32.6 us both) and
-    // int4 stacks nothing (4 x 4096, 12 layers: 545 / 549).
+    // with the glue fused in beats MFMA + a glue kernel of its own.  Where FC1 takes the same input on
+    // the matrix cores -- finds it as split halves then, and asks |x| < 65504 of it anyway -- the line
+    // is lower, and once more where the library's own glue forms that input (inside a stack).
+    // Measured, vector / matrix, us, B x d (r).  A step of 10 layers: 4 x 2048 (256) 239 / 246, (2048)
+    // 332 / 330; 5 x 2048 (512) 254 / 256; 8 x 1024 (128) 225 / 223; 4 x 3072 (512) 280 / 274; 8 x 1536
+    // (256) 262 / 237; 3 x 5120 (256) 388 / 385; 4 x 4096 (256) 343 / 334, (2048) 510 / 462.  One layer
+    // alone: 8 x 1536 (256) 22.0 / 23.6, (1536) 26.7 / 24.1; 4 x 3072 (512) 24.7 / 24.1; 7 x 2048 (256)
+    // 24.1 / 23.8; 3 x 5120 (1024) 36.7 / 35.8; 4 x 4096 (256) 29.0 / 27.6, (2048) 40.3 / 37.9.
+    // pf_predict and int4 layers keep fp32's range up to 20480 (int4 4 x 4096, 12 layers: 545 / 549).
     int hidden_mfma_min_elems = 20480;
-    int hidden_mfma_min_elems_glue = 15360;
+    int hidden_mfma_min_elems_fc1 = 15360;
+    int hidden_mfma_min_elems_glue = 11264;
     int lds_budget = kLdsDefault;  // dynamic LDS a kernel of this context may request
     int down_split = 0;            // PF_OPT_DOWN_SPLIT: row groups of FC2 (0 = from the CU count)
     int mfma_min_batch = 4;        // FC1 goes to the matrix cores from this batch size on
@@ -317,16 +320,26 @@ inline bool pred_mfma(const pf_ctx *ctx, const pf_layer_desc &D, int K, int B)
     return B >= mfma_from(ctx, D) && K % 32 == 0 && ctx->lds_budget > kLdsDefault;
 }
 
+// Whether FC1 over a predicted list runs on the matrix cores.
+inline bool up_mfma(const pf_ctx *ctx, const pf_layer_desc &D, int B)
+{
+    return D.wtype == PF_W_FP16 && B >= mfma_from(ctx, D) && D.d % 32 == 0 &&
+           pf::up_mfma_lds_bytes(D.ffn, true, D.act != PF_ACT_RELU) <= (size_t)ctx->lds_budget;
+}
+
 // Predictor hidden layer.  With glue_y the layer input is formed inside the kernel as
-// norm(x + glue_y) and also written to x_new.
+// norm(x + glue_y) and also written to x_new.  alone: no FC1 takes the input after it.
 pf_status launch_hidden(pf_ctx *ctx, const pf_layer *L, const float *x, const float *glue_y,
-                        int glue_ny, float *x_new, int B, hipStream_t st, const int32_t *skip = nullptr)
+                        int glue_ny, float *x_new, int B, hipStream_t st, const int32_t *skip = nullptr,
+                        bool alone = false)
 {
     const pf_layer_desc &D = L->desc;
     if (!L->w.p1 || !L->w.p2) return fail(ctx, PF_EINVAL, "layer has no predictor weights");
     const __half *p1 = static_cast<const __half *>(L->w.p1);
-    const int min_elems =
-        glue_y && D.wtype == PF_W_FP16 ? ctx->hidden_mfma_min_elems_glue : ctx->hidden_mfma_min_elems;
+    const bool with_fc1 = !alone && !ctx->split_off && up_mfma(ctx, D, B);
+    const int min_elems = !with_fc1 ? ctx->hidden_mfma_min_elems
+                          : glue_y  ? ctx->hidden_mfma_min_elems_glue
+                                    : ctx->hidden_mfma_min_elems_fc1;
     if (pred_mfma(ctx, D, D.d, B) && (size_t)B * (size_t)D.d > (size_t)min_elems) {
         // a batch on the matrix cores; the glue, if any, as a kernel of its own in front
         if (glue_y) {
@@ -389,9 +402,9 @@ inline int pred_out_words(const pf_layer *L) { return L->desc.ffn / 64 - L->alwa
 // Predictor: hidden layer, then output layer + ballot into mask words.
 pf_status launch_predict(pf_ctx *ctx, const pf_layer *L, const float *x, const float *glue_y,
                          int glue_ny, float *x_new, int B, float *scores, uint64_t *mask_words,
-                         hipStream_t st, const int32_t *skip = nullptr)
+                         hipStream_t st, const int32_t *skip = nullptr, bool alone = false)
 {
-    pf_status s = launch_hidden(ctx, L, x, glue_y, glue_ny, x_new, B, st, skip);
+    pf_status s = launch_hidden(ctx, L, x, glue_y, glue_ny, x_new, B, st, skip, alone);
     if (s != PF_OK) return s;
     const pf_layer_desc &D = L->desc;
     const __half *p2 = static_cast<const __half *>(L->w.p2);
@@ -1530,7 +1543,7 @@ pf_status pf_predict(pf_ctx *ctx, const pf_layer *layer, const float *x, int B, 
     if (s != PF_OK) return s;
     if (!mask_words) return fail(ctx, PF_EINVAL, "mask_words is null");
     return launch_predict(ctx, layer, x, nullptr, 0, nullptr, B, scores, mask_words,
-                          static_cast<hipStream_t>(stream));
+                          static_cast<hipStream_t>(stream), nullptr, true);
 }
 
 pf_status pf_compact(pf_ctx *ctx, const uint64_t *mask_words, int ffn, int32_t *idx, int32_t *count,
@@ -1744,7 +1757,8 @@ pf_status pf_ctx_set_option(pf_ctx *ctx, int key, int value)
             return PF_OK;
         case PF_OPT_HIDDEN_MFMA_MIN_ELEMS:
             if (value < 0) break;
-            ctx->hidden_mfma_min_elems = ctx->hidden_mfma_min_elems_glue = value;
+            ctx->hidden_mfma_min_elems = value;
+            ctx->hidden_mfma_min_elems_fc1 = ctx->hidden_mfma_min_elems_glue = value;
             return PF_OK;
         case PF_OPT_UP_GRID:
             if (value < 0 || value > 65535) break;

@@ -1,6 +1,6 @@
 """Which form of the predictor's hidden layer a batch takes, and that the matrix-core form is no less
-accurate than the vector form.  Inputs from outside stay on the vector units up to B * d = 20480:
-fp32 activations over all of fp32's range, whatever the weight type of the layer."""
+accurate than the vector form.  Up to B * d = 20480 pf_predict, and everything on int4 layers, stays on
+the vector units: fp32 activations over all of fp32's range."""
 import math
 
 import pytest
@@ -49,11 +49,20 @@ def test_predict_with_an_activation_beyond_fp16(pf, B, d, wtype):
     assert torch.equal(bits[clear], (ref > cfg.threshold).any(0)[clear])
     # the vector form, not another of the same accuracy
     assert torch.equal(scores, _predict(pf, cfg, lay, x, 1 << 30)[0])
+    if wtype == wl.W_INT4_G128:     # the layer step lists the same neurons, and its FC1 takes them
+        ctx = pf.Context(cfg.d, cfg.ffn, cfg.r, max_batch=B)
+        L = pf.Layer.from_workload(ctx, cfg, lay)
+        y = torch.full((B, d), float("nan"), device="cuda")
+        ctx.layer_step(L, x, y)
+        torch.cuda.synchronize()
+        got = torch.empty_like(words)
+        pf.copy_from_device_address(got, ctx.last_active()[0])
+        assert torch.equal(got, words) and bool(torch.isfinite(y).all())
 
 
-def test_stack_takes_the_matrix_cores_behind_its_own_glue(pf):
-    """Between 15360 and 20480 the inner layers of an fp16 stack run the matrix-core form, those of an
-    int4 stack the vector form."""
+def test_stack_takes_the_matrix_cores_where_fc1_does(pf):
+    """Between 15360 and 20480 the layers of an fp16 stack run the matrix-core form (a split or glue
+    kernel in front of each), those of an int4 stack the vector form."""
     for wtype in (wl.W_FP16, wl.W_INT4_G128):
         cfg = small_cfg(d=4096, ffn=512, r=128, wtype=wtype, rate=0.3, layers=3)
         lays = [wl.make_layer(cfg, l, 5, device="cuda") for l in range(3)]
@@ -68,7 +77,7 @@ def test_stack_takes_the_matrix_cores_behind_its_own_glue(pf):
             ctx.stack_step([pf.Layer.from_workload(ctx, cfg, t) for t in lays], x, out[-1])
             glues = ctx.profile_end()["k_glue"][0]
             torch.cuda.synchronize()
-            assert glues == (3 if wtype == wl.W_FP16 and min_elems is None else 1)
+            assert glues == (4 if wtype == wl.W_FP16 and min_elems is None else 1)
         assert (out[0] - out[1]).abs().max() < 1e-4
 
 
