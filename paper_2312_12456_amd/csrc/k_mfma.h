@@ -698,6 +698,7 @@ __device__ __forceinline__ float half_f32(uint32_t pair, int i)
     return (float)h;
 }
 
+template <bool SHORT = false>
 __device__ __forceinline__ void down2_mfma_body(
     float *red, const int tile, const int g, const int P, const __half *w_down, const float *b_down,
     const float *h, const int32_t *idx, const int32_t *count_p, float *part, int B, int hs, int d, int ffn)
@@ -830,8 +831,18 @@ __device__ __forceinline__ void down2_mfma_body(
     uint4 w[8];
     Down2mOps o;
     float f;
+    Down2Round<4> rs4;
+    if (SHORT) down2_request<4>(rs4, 0, wave * 8 + rs, g, P, h, idx, ffn);
     request(ra, c);
     const int n = min(max(wave_uniform(*count_p), 0), ffn);
+    if (SHORT && n <= kDown2RowsPerLoad * Down2Shape<4>::U * P) {  // the same in all workgroups
+        float a4[32];
+#pragma unroll
+        for (int e = 0; e < 32; ++e) a4[e] = 0.f;
+        down2_round<4>(a4, rs4, wd, 0, wave * 8 + rs, g, P, tile * kDown2Cols + cl * 8, n, d, ffn);
+        down2_finish<4>(a4, reinterpret_cast<float(*)[4][kDown2Cols]>(red), tile, g, b_down, part, d);
+        return;
+    }
     const int nc = (n + kDown2mRows - 1) / kDown2mRows;
     for (; c < nc; c += step) {
         request(rb, c + step);  // ahead of the rows, so that the next chunk's do not wait for it
@@ -885,13 +896,21 @@ __device__ __forceinline__ void down2_mfma_body(
 }
 
 // grid = (d / 64 tiles, P), block = 512.
+// SHORT (batch 4): a list that one round of the vector form covers (256 rows per row group) is added up
+// by that form's code -- its waves then share the rows evenly, where most waves here would have no
+// chunk and the others 0.8 us of work after their rows have arrived.  Both forms' first loads leave
+// together, as the length of the list is only known on the device.  A step of 12 layers, us, vector
+// kernel / always this form / this rule: 768 x 3072, 15 % active 218 / 225 / 218; 2048 x 5120, 8 %
+// 265 / 273 / 265, 15 % (longer lists) 286 / 282 / 279; 768 x 3072, 4 % 211 / 215 / 213.  From batch 5
+// on the vector form has no such range.
+template <bool SHORT>
 __global__ __launch_bounds__(kDown2Threads, 4) void k_down2_mfma(
     const __half *__restrict__ w_down, const float *__restrict__ b_down, const float *__restrict__ h,
     const int32_t *__restrict__ idx, const int32_t *__restrict__ count_p, float *__restrict__ part, int B, int hs,
     int d, int ffn)
 {
     __shared__ __align__(16) float red[kDown2mRedFloats];
-    down2_mfma_body(red, (int)blockIdx.x, (int)blockIdx.y, (int)gridDim.y, w_down, b_down, h, idx, count_p,
+    down2_mfma_body<SHORT>(red, (int)blockIdx.x, (int)blockIdx.y, (int)gridDim.y, w_down, b_down, h, idx, count_p,
                            part, B, hs, d, ffn);
 }
 

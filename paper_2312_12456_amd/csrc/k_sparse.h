@@ -224,79 +224,77 @@ constexpr int kDown2Cols = 64;
 constexpr int kDown2RowsPerLoad = kDown2Threads / 8;
 constexpr int kDown2MaxSplit = 4;
 
+// Rows of a round that a lane loads (U), and the tokens padded to a power of two for the halving
+// butterfly of the epilogue (BP): token b, column e of the lane -> acc[8 b + e].
 template <int B>
-__device__ __forceinline__ void down2_body(
-    float (*red)[B][kDown2Cols], const int tile, const int g, const int P,
-    const __half *__restrict__ w_down, const float *__restrict__ b_down,
-    const float *__restrict__ h, const int32_t *__restrict__ idx,
-    const int32_t *__restrict__ count_p, float *__restrict__ part, int d, int ffn)
+struct Down2Shape {
+    static constexpr int U = (B <= 2) ? 8 : 4;
+    static constexpr int BP = B <= 1 ? 1 : B <= 2 ? 2 : B <= 4 ? 4 : 8;
+};
+template <int B>
+struct Down2Round {
+    float h[Down2Shape<B>::U][B];
+    int iv[Down2Shape<B>::U];
+};
+
+// Loads of the round from r0 on that depend on the slot number only.
+template <int B>
+__device__ __forceinline__ void down2_request(Down2Round<B> &r, int r0, int rslot, int g, int P,
+                                              const float *__restrict__ h, const int32_t *__restrict__ idx, int ffn)
 {
-    constexpr int U = (B <= 2) ? 8 : 4;
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    const int cl = lane & 7;                      // which 16 bytes of the row's 128-byte line
-    const int rslot = wave * 8 + (lane >> 3);     // row slot of this lane inside a load
-    const int col = tile * kDown2Cols + cl * 8;
-    const bool colok = col < d;
-    const rsrc_t wd = make_rsrc(w_down, (uint32_t)ffn * (uint32_t)d * 2u);
-
-    PF_TSTAMP(3, 0);
-    // token b, column e of this lane -> acc[8 b + e]; padded to a power of two tokens for the
-    // halving butterfly of the epilogue
-    constexpr int BP = B <= 1 ? 1 : B <= 2 ? 2 : B <= 4 ? 4 : 8;
-    float acc[BP * 8];
 #pragma unroll
-    for (int f = 0; f < BP * 8; ++f) acc[f] = 0.f;
-
-    int n = 0;
-    bool have_n = false;
-    for (int r0 = 0; r0 == 0 || r0 * P < n; r0 += kDown2RowsPerLoad * U) {
-        uint4 w[U];
-        float hv[U][B];
-        int iv[U];
-#pragma unroll
-        for (int u = 0; u < U; ++u) {  // loads that depend on the slot number only
-            const int jc = min((r0 + u * kDown2RowsPerLoad + rslot) * P + g, ffn - 1);
-            iv[u] = idx[jc];
-            load_h_slot<B>(h, jc, hv[u]);
-        }
-        if (!have_n) {
-            n = min(max(*count_p, 0), ffn);
-            have_n = true;
-            PF_TSTAMP(3, 1);
-        }
-#pragma unroll
-        for (int u = 0; u < U; ++u) {
-            const int jj = (r0 + u * kDown2RowsPerLoad + rslot) * P + g;
-            const bool ok = jj < n && (unsigned)iv[u] < (unsigned)ffn;
-            w[u] = ld16_stream(wd, (ok && colok) ? ((uint32_t)iv[u] * (uint32_t)d + (uint32_t)col) * 2u
-                                                 : kOobOffset);
-#pragma unroll
-            for (int b = 0; b < B; ++b) hv[u][b] = ok ? hv[u][b] : 0.f;
-        }
-#pragma unroll
-        for (int u = 0; u < U; ++u) {
-            const float f0 = h_lo(w[u].x), f1 = h_hi(w[u].x), f2 = h_lo(w[u].y), f3 = h_hi(w[u].y);
-            const float f4 = h_lo(w[u].z), f5 = h_hi(w[u].z), f6 = h_lo(w[u].w), f7 = h_hi(w[u].w);
-#pragma unroll
-            for (int b = 0; b < B; ++b) {
-                const float s = hv[u][b];
-                acc[8 * b + 0] = fmaf(s, f0, acc[8 * b + 0]);
-                acc[8 * b + 1] = fmaf(s, f1, acc[8 * b + 1]);
-                acc[8 * b + 2] = fmaf(s, f2, acc[8 * b + 2]);
-                acc[8 * b + 3] = fmaf(s, f3, acc[8 * b + 3]);
-                acc[8 * b + 4] = fmaf(s, f4, acc[8 * b + 4]);
-                acc[8 * b + 5] = fmaf(s, f5, acc[8 * b + 5]);
-                acc[8 * b + 6] = fmaf(s, f6, acc[8 * b + 6]);
-                acc[8 * b + 7] = fmaf(s, f7, acc[8 * b + 7]);
-            }
-        }
-        if (r0 == 0) PF_TSTAMP(3, 2);
+    for (int u = 0; u < Down2Shape<B>::U; ++u) {
+        const int jc = min((r0 + u * kDown2RowsPerLoad + rslot) * P + g, ffn - 1);
+        r.iv[u] = idx[jc];
+        load_h_slot<B>(h, jc, r.h[u]);
     }
-    PF_TSTAMP(3, 3);
+}
 
-    // sum the 8 row slots of the wave (lane bits 5, 4, 3) with a halving butterfly: a lane ends
-    // with BP of its 8 BP values, flat indices [BP * slot, BP * (slot + 1)); then the 8 waves
-    // through LDS
+// The rows of a round of a list of n, into acc.
+template <int B>
+__device__ __forceinline__ void down2_round(float (&acc)[Down2Shape<B>::BP * 8], Down2Round<B> &r, rsrc_t wd, int r0,
+                                            int rslot, int g, int P, int col, int n, int d, int ffn)
+{
+    constexpr int U = Down2Shape<B>::U;
+    uint4 w[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+        const int jj = (r0 + u * kDown2RowsPerLoad + rslot) * P + g;
+        const bool ok = jj < n && (unsigned)r.iv[u] < (unsigned)ffn;
+        w[u] = ld16_stream(wd, (ok && col < d) ? ((uint32_t)r.iv[u] * (uint32_t)d + (uint32_t)col) * 2u
+                                               : kOobOffset);
+#pragma unroll
+        for (int b = 0; b < B; ++b) r.h[u][b] = ok ? r.h[u][b] : 0.f;
+    }
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+        const float f0 = h_lo(w[u].x), f1 = h_hi(w[u].x), f2 = h_lo(w[u].y), f3 = h_hi(w[u].y);
+        const float f4 = h_lo(w[u].z), f5 = h_hi(w[u].z), f6 = h_lo(w[u].w), f7 = h_hi(w[u].w);
+#pragma unroll
+        for (int b = 0; b < B; ++b) {
+            const float s = r.h[u][b];
+            acc[8 * b + 0] = fmaf(s, f0, acc[8 * b + 0]);
+            acc[8 * b + 1] = fmaf(s, f1, acc[8 * b + 1]);
+            acc[8 * b + 2] = fmaf(s, f2, acc[8 * b + 2]);
+            acc[8 * b + 3] = fmaf(s, f3, acc[8 * b + 3]);
+            acc[8 * b + 4] = fmaf(s, f4, acc[8 * b + 4]);
+            acc[8 * b + 5] = fmaf(s, f5, acc[8 * b + 5]);
+            acc[8 * b + 6] = fmaf(s, f6, acc[8 * b + 6]);
+            acc[8 * b + 7] = fmaf(s, f7, acc[8 * b + 7]);
+        }
+    }
+}
+
+// Sums over the 8 row slots of each wave (lane bits 5, 4, 3) with a halving butterfly -- a lane ends
+// with BP of its 8 BP values, flat indices [BP * slot, BP * (slot + 1)) --, then over the 8 waves
+// through LDS, to part[g].
+template <int B>
+__device__ __forceinline__ void down2_finish(float (&acc)[Down2Shape<B>::BP * 8], float (*red)[B][kDown2Cols],
+                                             int tile, int g, const float *__restrict__ b_down,
+                                             float *__restrict__ part, int d)
+{
+    constexpr int BP = Down2Shape<B>::BP;
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, cl = lane & 7;
     butterfly_halve<32, BP * 4>(acc, lane);
     butterfly_halve<16, BP * 2>(acc, lane);
     butterfly_halve<8, BP>(acc, lane);
@@ -320,6 +318,41 @@ __device__ __forceinline__ void down2_body(
             part[((size_t)g * B + b) * d + oc] = s;
         }
     }
+}
+
+template <int B>
+__device__ __forceinline__ void down2_body(
+    float (*red)[B][kDown2Cols], const int tile, const int g, const int P,
+    const __half *__restrict__ w_down, const float *__restrict__ b_down,
+    const float *__restrict__ h, const int32_t *__restrict__ idx,
+    const int32_t *__restrict__ count_p, float *__restrict__ part, int d, int ffn)
+{
+    constexpr int U = Down2Shape<B>::U, BP = Down2Shape<B>::BP;
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int rslot = wave * 8 + (lane >> 3);             // row slot of this lane inside a load
+    const int col = tile * kDown2Cols + (lane & 7) * 8;   // its 16 bytes of the row's 128-byte line
+    const rsrc_t wd = make_rsrc(w_down, (uint32_t)ffn * (uint32_t)d * 2u);
+
+    PF_TSTAMP(3, 0);
+    float acc[BP * 8];
+#pragma unroll
+    for (int f = 0; f < BP * 8; ++f) acc[f] = 0.f;
+
+    int n = 0;
+    bool have_n = false;
+    for (int r0 = 0; r0 == 0 || r0 * P < n; r0 += kDown2RowsPerLoad * U) {
+        Down2Round<B> r;
+        down2_request<B>(r, r0, rslot, g, P, h, idx, ffn);
+        if (!have_n) {
+            n = min(max(*count_p, 0), ffn);
+            have_n = true;
+            PF_TSTAMP(3, 1);
+        }
+        down2_round<B>(acc, r, wd, r0, rslot, g, P, col, n, d, ffn);
+        if (r0 == 0) PF_TSTAMP(3, 2);
+    }
+    PF_TSTAMP(3, 3);
+    down2_finish<B>(acc, red, tile, g, b_down, part, d);
     PF_TSTAMP(3, 5);
 }
 

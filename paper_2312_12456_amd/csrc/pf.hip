@@ -604,8 +604,11 @@ pf_status launch_sparse(pf_ctx *ctx, const pf_layer *L, const float *x, int B,
         // batch 3 the two are equal (OPT-30B shape, 8 layers: 501 us both).  Widths that are no
         // multiple of 32 run the vector FC1 and the vector FC2 behind it.
         if (mfma && B >= 4) {
-            PF_LAUNCH(ps, pf::k_down2_mfma, dim3(tiles, P), dim3(pf::kDown2Threads), 0, st, w_down,
-                      L->w.b_down, (const float *)ctx->h, idx, count, part, B, pf::h_stride(B), D.d, D.ffn);
+#define PF_DNM(SHORT)                                                                                   \
+    PF_LAUNCH(ps, pf::k_down2_mfma<SHORT>, dim3(tiles, P), dim3(pf::kDown2Threads), 0, st, w_down,        \
+              L->w.b_down, (const float *)ctx->h, idx, count, part, B, pf::h_stride(B), D.d, D.ffn)
+            if (B == 4) { PF_DNM(true); } else { PF_DNM(false); }
+#undef PF_DNM
         } else {
             PF_SWITCH_B(B, PF_LAUNCH(ps, pf::k_down2<BT>, dim3(tiles, P), dim3(pf::kDown2Threads), 0,
                                       st, w_down, L->w.b_down, ctx->h, idx, count, part, D.d, D.ffn));
