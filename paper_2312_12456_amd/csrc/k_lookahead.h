@@ -84,7 +84,7 @@ __global__ __launch_bounds__(kDown2Threads) void k_la_down_out(
 // ---------------------------------------------------------------------------------------
 // The same two launches for batches on the matrix cores (batch >= 4, or 3 with long rows),
 // from the matrix-core kernels' bodies.  These read the layer input from memory, as split
-// fp16 planes, so a glue kernel of its own (or k_split for the first layer) runs in front of
+// fp16 halves, so a glue kernel of its own (or k_split for the first layer) runs in front of
 // the first launch.  Ungated layers: two workgroups of
 // either role fit a CU.  The gated FC1 needs 128 KB of LDS per workgroup, so there a CU holds
 // one workgroup at a time and the hidden-layer role follows FC1 rather than sharing the CUs.

@@ -3,14 +3,13 @@
 // rows form a dense [k x d] block that multiplies [d x B]).  At batch 1 the row-sparse GEMV is
 // pure HBM streaming; from a few tokens on, B FMAs and B LDS reads per weight make the vector
 // path the limiter before HBM saturates, and v_mfma_f32_16x16x32_f16 does the same work in a
-// fraction of the issue slots.  M = 16 gathered rows, N = 16 batch columns (tokens >= B read
-// as zero), K = 32 elements of d per instruction.
+// fraction of the issue slots.  M = 16 gathered rows, N = 16 columns (one per half of each token;
+// the others read as zero), K = 32 elements of d per instruction.
 // Operand layout (verified on the device): lane l supplies A[row l%16][8 halfs from k = 8*(l/16)]
 // and B[same 8 k][col l%16]; it receives C[rows 4*(l/16) .. +3][col l%16].
-// x enters as fp16 hi + fp16 lo (split_f32: to 2^-24 of x).  Where the
-// halves come ready-made (XS), both ride in one MFMA, as a batch has at most 8 tokens: with hs =
-// h_stride(B) column b multiplies the hi half of token b and column hs + b its lo half.  Where a
-// kernel splits fp32 activations itself, each step issues two MFMAs into two tiles (lanes of both
+// x enters as fp16 hi + fp16 lo (split_f32: to 2^-24 of x).  Where the halves come ready-made (XS),
+// both ride in one MFMA, as a batch has at most 8 tokens: with hs = h_stride(B) column b multiplies
+// the hi half of token b and column hs + b its lo half.  Where a kernel splits fp32 activations itself, each step issues two MFMAs into two tiles (lanes of both
 // column ranges splitting the same values measured 2 - 6 % slower: OPT-6.7B shape with every neuron
 // listed, batch 8, 54.4 -> 57.7 us).  Each wave's two sums are added first, then the waves' (see
 // put_tile): both forms give the same bits.
@@ -328,7 +327,7 @@ __device__ __forceinline__ void up_mfma_passes(const UpMfmaArgs &a)
 // as one 16-row tile with 256-element chunks, a larger one in passes of 32 rows (two tiles)
 // with 128-element chunks.  The 8 waves of a block take the chunks round-robin (wave w:
 // chunks w, w + 8, ...) for the same rows and their C tiles are added in LDS in wave order.
-// d % 32 == 0, B <= 16.
+// d % 32 == 0, B <= 8: both halves of every token have a column.
 // The body takes its block number and the number of blocks of its role explicitly, so that a
 // launch can run it in a range of its blocks beside another role.  Its pointer parameters carry
 // no restrict qualifier on purpose: a wave reads back from LDS what its own global -> LDS loads

@@ -24,6 +24,7 @@
 namespace {
 
 constexpr int kMaxBatch = 8;
+static_assert(2 * pf::h_stride(kMaxBatch) <= 16, "both halves of every token have a matrix-core column");
 constexpr int kMaxFfn = 4096 * 64;      // the in-kernel bit select handles 4096 mask words
 constexpr int kProfPairsCap = 32768;    // event pairs one profiling pass may record
 constexpr int kLdsMax = 160 * 1024;     // LDS per workgroup on gfx950
@@ -716,7 +717,7 @@ pf_status launch_glue(pf_ctx *ctx, const float *x, const float *y, int ny, int d
         xs = ctx->xsplit[ctx->split_cur];
         ctx->split_src = x_next;
     } else if (ctx->split_src == x_next) {
-        ctx->split_src = nullptr;  // its planes go stale
+        ctx->split_src = nullptr;  // its halves go stale
     }
     {
         ProfScope ps(ctx, K_GLUE);
@@ -740,8 +741,8 @@ pf_status ensure_split(pf_ctx *ctx, const float *x, int B, int d, hipStream_t st
 {
     *xs = split_of(ctx, x);
     if (*xs) return PF_OK;
-    // no planes: a context without the buffers, an odd shape, or kernels being enqueued on a
-    // second stream (the planes' bookkeeping follows one stream); the caller reads fp32 then
+    // no halves: a context without the buffers, an odd shape, or kernels being enqueued on a
+    // second stream (the bookkeeping follows one stream); the caller reads fp32 then
     if (!ctx->xsplit[0] || d % 8 != 0 || ctx->split_off) return PF_OK;
     ctx->split_cur ^= 1;
     __half *dst = ctx->xsplit[ctx->split_cur];
