@@ -650,9 +650,9 @@ __global__ __launch_bounds__(kMfmaThreads) void k_rows_mfma(
 // 24 MFMAs per 8 KB of weights).  A lane's B operand is then h of exactly the rows that it loads.
 // h enters with all of its 24 bits, as three fp16 parts of 8 bits each: h * 2^s = p1 + p2 / 2^8 +
 // p3 / 2^16, s per chunk, token and slot parity such that the largest |h| lands in [2^14, 2^15).
-// The split is exact down to 2^-31 of that largest value; a chunk with a smaller h other than zero
-// is added up without the matrix cores (plain_chunk), so that a column in which the large values
-// have no weight is as accurate as any other.
+// The split is exact down to 2^-31 of that largest value; a wave that meets a smaller h other than
+// zero forms its sums without the matrix cores, so that a column in which the large values have no
+// weight is as accurate as any other.
 // Precision: a matrix instruction takes its products in four groups of 8 (k = 0..7, 8..15, ...; all
 // of this measured on the device).  In each group it cuts the products, towards zero, and the sum so
 // far, towards minus infinity, at 2^-26 of (a bound on) the largest product, adds, and rounds to
@@ -664,7 +664,7 @@ __global__ __launch_bounds__(kMfmaThreads) void k_rows_mfma(
 // added in a chain: 1500 x 2048 9.3 / 10.4 -> 8.0; 2600 x 4096 9.6 / 11.4 -> 8.3; 5000 x 5120 10.6 /
 // 11.6 -> 8.7; 28672 x 7168 15.9 / 13.4 -> 10.8.
 // Bound by memory: ids and h of the next chunk are requested in front of the rows of this one, so
-// a wave waits for one round trip per 8 KB.  124 registers leave room for two workgroups per CU
+// a wave waits for one round trip per 8 KB.  126 registers leave room for two workgroups per CU
 // (the second launch of the look-ahead form needs that).
 // Vector form -> this one, us: OPT-30B shape batch 8 (65 MB) 21.9 -> 17.4, LLaMA-13B shape batch 4
 // (44 MB) 14.8 -> 12.3, all 16384 neurons of an OPT-6.7B layer at batch 4 (134 MB) 35.3 -> 25.7.
@@ -722,8 +722,7 @@ __device__ __forceinline__ void down2_mfma_body(
         const int j = c * kDown2mRows + lane;
         r.iv = (int)__builtin_amdgcn_raw_buffer_load_b32(ir, j < ffn ? j * 4 : (int)kOobOffset, 0, 0);
     };
-    // weight rows of chunk c; h of slots without a row becomes 0.  Returns the byte offset of the row
-    // of slot lane.
+    // weight rows of chunk c; h of slots without a row becomes 0
     auto load_rows = [&](uint4 (&w)[8], Down2mIds &r, int c, int n) {
         const bool ok = c * kDown2mRows + lane < n && (unsigned)r.iv < (unsigned)ffn;
         const uint32_t row = ok ? (uint32_t)r.iv * (uint32_t)d * 2u : kOobOffset;
@@ -733,7 +732,6 @@ __device__ __forceinline__ void down2_mfma_body(
             w[u] = ld16_stream(wd, colok && ro != kOobOffset ? ro + colbyte : kOobOffset);
             r.h[u] = ro != kOobOffset ? r.h[u] : 0.f;
         }
-        return row;
     };
     float4v_t acc[8];  // [t][i]: column 8 (m % 8) + t of m = 4 (lane / 16) + i
 #pragma unroll
@@ -798,32 +796,6 @@ __device__ __forceinline__ void down2_mfma_body(
     // l / 32, columns 32 (l / 16 % 2) + 8 i + t, token l % 8.
     const int par = lane >> 5, chalf = (lane >> 4) & 1;
     const bool mine = par == ((lane >> 3) & 1);
-    // A chunk without the matrix cores: the same sums in fp32, one row after the other.
-    auto plain_chunk = [&](uint32_t row, int c) {
-        float4v_t sum[8];
-#pragma unroll
-        for (int t = 0; t < 8; ++t) sum[t] = (float4v_t){0.f, 0.f, 0.f, 0.f};
-#pragma unroll 1
-        for (int s = 0; s < kDown2mRows / 2; ++s) {
-            const int slot = 2 * s + par, j = c * kDown2mRows + slot;
-            const uint32_t ro = (uint32_t)__shfl((int)row, slot, 64);
-            const bool ok = mine && cl < B && ro != kOobOffset;  // then j < ffn
-            const float hv = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(
-                hr, ok ? (int)((uint32_t)(j * hs + cl) * 4u) : (int)kOobOffset, 0, 0));
-#pragma unroll
-            for (int i = 0; i < 4; ++i) {
-                const int col = tile * kDown2Cols + 32 * chalf + 8 * i;
-                const uint4 q = ld16_cached(wd, ok && col < d ? ro + (uint32_t)col * 2u : kOobOffset);
-                const uint32_t qd[4] = {q.x, q.y, q.z, q.w};
-#pragma unroll
-                for (int t = 0; t < 8; ++t)
-                    sum[t][i] = fmaf(hv, (t & 1) ? h_hi(qd[t / 2]) : h_lo(qd[t / 2]), sum[t][i]);
-            }
-        }
-#pragma unroll
-        for (int t = 0; t < 8; ++t) acc[t] += sum[t];
-    };
-
     const int step = kDown2Waves * P;
     int c = wave * P + g;
     Down2mIds ra, rb;
@@ -843,39 +815,71 @@ __device__ __forceinline__ void down2_mfma_body(
         return;
     }
     const int nc = (n + kDown2mRows - 1) / kDown2mRows;
+    bool again = false;
     for (; c < nc; c += step) {
         request(rb, c + step);  // ahead of the rows, so that the next chunk's do not wait for it
-        const uint32_t row = load_rows(w, ra, c, n);
-        if (__ballot(operands(o, f, ra)) == 0)
-            multiply(w, o, f);
-        else
-            plain_chunk(row, c);
+        load_rows(w, ra, c, n);
+        again |= operands(o, f, ra);
+        multiply(w, o, f);
         ra = rb;
     }
-    // An infinite weight or h may have met a part of h that is zero, or another of the other sign:
-    // sums that are not finite are formed once more without the parts.
+    // An infinite weight or h may have met a part of h that is zero, or another of the other sign.
     float nan = 0.f;
 #pragma unroll
     for (int t = 0; t < 8; ++t)
 #pragma unroll
         for (int i = 0; i < 4; ++i) nan = fmaf(acc[t][i], 0.f, nan);
-    if (__ballot(mine && nan != 0.f) != 0) {
-#pragma unroll
-        for (int t = 0; t < 8; ++t) acc[t] = (float4v_t){0.f, 0.f, 0.f, 0.f};
-#pragma unroll 1
-        for (c = wave * P + g; c < nc; c += step) {
-            const int j = c * kDown2mRows + lane;
-            const int i = (int)__builtin_amdgcn_raw_buffer_load_b32(ir, j < n ? j * 4 : (int)kOobOffset, 0, 0);
-            plain_chunk(j < n && (unsigned)i < (unsigned)ffn ? (uint32_t)i * (uint32_t)d * 2u : kOobOffset, c);
-        }
-    }
+    again |= mine && nan != 0.f;
 
-    if (mine) {
-        float *to = red + ((wave * 2 + par) * 8 + cl) * kDown2mPitch + 32 * chalf;
+    float *to = red + ((wave * 2 + par) * 8 + cl) * kDown2mPitch + 32 * chalf;
+    if (__ballot(again) == 0) {
+        if (mine) {
 #pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                *reinterpret_cast<float4 *>(to + 8 * i) = make_float4(acc[0][i], acc[1][i], acc[2][i], acc[3][i]);
+                *reinterpret_cast<float4 *>(to + 8 * i + 4) = make_float4(acc[4][i], acc[5][i], acc[6][i], acc[7][i]);
+            }
+        }
+    } else {
+        // Sums that the parts do not hold, or that are not finite: all of the wave's once more in fp32,
+        // row by row.  Hardly ever taken, so it is kept small and out of the loop: one copy of it in the
+        // loop and one behind slowed down the workgroups of the other role in the look-ahead launch
+        // (OPT-30B shape, batch 4: 26.5 -> 28.3 us).
+#pragma unroll 1
         for (int i = 0; i < 4; ++i) {
-            *reinterpret_cast<float4 *>(to + 8 * i) = make_float4(acc[0][i], acc[1][i], acc[2][i], acc[3][i]);
-            *reinterpret_cast<float4 *>(to + 8 * i + 4) = make_float4(acc[4][i], acc[5][i], acc[6][i], acc[7][i]);
+            const int col = tile * kDown2Cols + 32 * chalf + 8 * i;
+            float tot[8];
+#pragma unroll
+            for (int t = 0; t < 8; ++t) tot[t] = 0.f;
+#pragma unroll 1
+            for (c = wave * P + g; c < nc; c += step) {
+                const int jl = c * kDown2mRows + lane;
+                const int il = (int)__builtin_amdgcn_raw_buffer_load_b32(ir, jl < n ? jl * 4 : (int)kOobOffset, 0, 0);
+                const uint32_t row =
+                    jl < n && (unsigned)il < (unsigned)ffn ? (uint32_t)il * (uint32_t)d * 2u : kOobOffset;
+                float sum[8];
+#pragma unroll
+                for (int t = 0; t < 8; ++t) sum[t] = 0.f;
+#pragma unroll 1
+                for (int s = 0; s < kDown2mRows / 2; ++s) {
+                    const int slot = 2 * s + par, j = c * kDown2mRows + slot;
+                    const uint32_t ro = (uint32_t)__shfl((int)row, slot, 64);
+                    const bool ok = mine && cl < B && ro != kOobOffset;  // then j < n
+                    const float hv = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(
+                        hr, ok ? (int)((uint32_t)(j * hs + cl) * 4u) : (int)kOobOffset, 0, 0));
+                    const uint4 q = ld16_cached(wd, ok && col < d ? ro + (uint32_t)col * 2u : kOobOffset);
+                    const uint32_t qd[4] = {q.x, q.y, q.z, q.w};
+#pragma unroll
+                    for (int t = 0; t < 8; ++t)
+                        sum[t] = fmaf(hv, (t & 1) ? h_hi(qd[t / 2]) : h_lo(qd[t / 2]), sum[t]);
+                }
+#pragma unroll
+                for (int t = 0; t < 8; ++t) tot[t] += sum[t];
+            }
+            if (mine) {
+                *reinterpret_cast<float4 *>(to + 8 * i) = make_float4(tot[0], tot[1], tot[2], tot[3]);
+                *reinterpret_cast<float4 *>(to + 8 * i + 4) = make_float4(tot[4], tot[5], tot[6], tot[7]);
+            }
         }
     }
     __syncthreads();
