@@ -258,9 +258,9 @@ pf_status pf_ctx_set_lookahead(pf_ctx *ctx, int distance);
  *   PF_OPT_MFMA_MIN_BATCH   batch size from which FC1 and the predictor run on the matrix
  *                           cores (default rule: 4, and 3 where d > 4096); 0 = default rule
  *   PF_OPT_HIDDEN_MFMA_MIN_ELEMS  the predictor's hidden layer joins them only above this
- *                           B * d (default 20480; where an FC1 on the matrix cores takes the same
- *                           input 15360, inside a stack 11264; every value >= 0 is taken as given,
- *                           for all three)
+ *                           B * d (default 20480; 15360 where an FC1 on the matrix cores takes the
+ *                           same input or the library's glue forms it, 11264 where both do; every
+ *                           value >= 0 is taken as given, for all three)
  *   PF_OPT_UP_GRID          workgroups of the vector FC1 kernel (default 8 per CU; int4: 2)
  *   PF_OPT_MFMA_GRID        workgroups of the matrix-core FC1 kernel (default one per CU)
  *   PF_OPT_DOWN_SPLIT       row groups of FC2, 1 .. 4 (default CUs / column tiles, at most 4)

@@ -50,18 +50,21 @@ struct pf_ctx {
     int up_grid_cap_i4 = 512;
     int mfma_grid = 0;              // PF_OPT_MFMA_GRID: blocks of k_up_mfma (0 = from the CU count)
     // The hidden layer goes to the matrix cores only above this B * d: below it the vector kernel
-    // with the glue fused in beats MFMA + a glue kernel of its own.  Where FC1 takes the same input on
-    // the matrix cores -- finds it as split halves then, and asks |x| < 65504 of it anyway -- the line
-    // is lower, and once more where the library's own glue forms that input (inside a stack).
-    // Measured, vector / matrix, us, B x d (r).  A step of 10 layers: 4 x 2048 (256) 239 / 246, (2048)
-    // 332 / 330; 5 x 2048 (512) 254 / 256; 8 x 1024 (128) 225 / 223; 4 x 3072 (512) 280 / 274; 8 x 1536
-    // (256) 262 / 237; 3 x 5120 (256) 388 / 385; 4 x 4096 (256) 343 / 334, (2048) 510 / 462.  One layer
-    // alone: 8 x 1536 (256) 22.0 / 23.6, (1536) 26.7 / 24.1; 4 x 3072 (512) 24.7 / 24.1; 7 x 2048 (256)
-    // 24.1 / 23.8; 3 x 5120 (1024) 36.7 / 35.8; 4 x 4096 (256) 29.0 / 27.6, (2048) 40.3 / 37.9.
-    // pf_predict and int4 layers keep fp32's range up to 20480 (int4 4 x 4096, 12 layers: 545 / 549).
+    // with the glue fused in beats MFMA + a glue kernel of its own.  The line is lower where one of two
+    // things holds, and lowest where both do: FC1 takes the same input on the matrix cores (finds it as
+    // split halves then, and asks |x| < 65504 of it anyway); the library's own glue forms that input
+    // (inside a stack: |x| <= sqrt(d)).  Everything else keeps fp32's range up to 20480: pf_predict,
+    // single int4 layers, the first layer of an int4 stack.
+    // Measured, vector / matrix, us, B x d (r).  Both, a step of 10 layers: 4 x 2048 (256) 239 / 246,
+    // (2048) 332 / 330; 5 x 2048 (512) 254 / 256; 8 x 1024 (128) 225 / 223; 4 x 3072 (512) 280 / 274;
+    // 8 x 1536 (256) 262 / 237; 3 x 5120 (256) 388 / 385; 4 x 4096 (256) 343 / 334, (2048) 510 / 462.
+    // One fp16 layer by itself: 8 x 1536 (256) 22.0 / 23.6, (1536) 26.7 / 24.1; 4 x 3072 (512) 24.7 /
+    // 24.1; 7 x 2048 (256) 24.1 / 23.8; 3 x 5120 (1024) 36.7 / 35.8; 4 x 4096 (2048) 40.3 / 37.9.
+    // int4 stacks of 12 layers: 4 x 4096 (1024) 545 / 549, 4 x 5120 (1024) 872 / 868, 8 x 2304 (608)
+    // 1393 / 1355.
     int hidden_mfma_min_elems = 20480;
-    int hidden_mfma_min_elems_fc1 = 15360;
-    int hidden_mfma_min_elems_glue = 11264;
+    int hidden_mfma_min_elems_one = 15360;
+    int hidden_mfma_min_elems_both = 11264;
     int lds_budget = kLdsDefault;  // dynamic LDS a kernel of this context may request
     int down_split = 0;            // PF_OPT_DOWN_SPLIT: row groups of FC2 (0 = from the CU count)
     int mfma_min_batch = 4;        // FC1 goes to the matrix cores from this batch size on
@@ -337,10 +340,10 @@ pf_status launch_hidden(pf_ctx *ctx, const pf_layer *L, const float *x, const fl
     const pf_layer_desc &D = L->desc;
     if (!L->w.p1 || !L->w.p2) return fail(ctx, PF_EINVAL, "layer has no predictor weights");
     const __half *p1 = static_cast<const __half *>(L->w.p1);
-    const bool with_fc1 = !alone && !ctx->split_off && up_mfma(ctx, D, B);
-    const int min_elems = !with_fc1 ? ctx->hidden_mfma_min_elems
-                          : glue_y  ? ctx->hidden_mfma_min_elems_glue
-                                    : ctx->hidden_mfma_min_elems_fc1;
+    const bool fc1 = !ctx->split_off && up_mfma(ctx, D, B);
+    const int min_elems = alone || (!fc1 && !glue_y) ? ctx->hidden_mfma_min_elems
+                          : !fc1 || !glue_y          ? ctx->hidden_mfma_min_elems_one
+                                                     : ctx->hidden_mfma_min_elems_both;
     if (pred_mfma(ctx, D, D.d, B) && (size_t)B * (size_t)D.d > (size_t)min_elems) {
         // a batch on the matrix cores; the glue, if any, as a kernel of its own in front
         if (glue_y) {
@@ -439,9 +442,11 @@ pf_status launch_predict(pf_ctx *ctx, const pf_layer *L, const float *x, const f
 
 // Row groups of FC2 (P): with `tiles` column tiles the launch has tiles * P workgroups, each
 // over 1/P of the listed rows.  One round of workgroups (<= one per CU) costs 1/P; two
-// workgroups share a CU at about 1.6 x the time of one while the batch is small enough for two
-// to be resident (measured at 112 and 128 tiles; at batch 8 the second workgroup waits); more
-// rounds cost a round each.  Ties go to the smaller P (fewer partial sums to add).
+// workgroups share a CU at about 1.6 x the time of one up to batch 4 (measured at 112 and 128
+// tiles); more rounds cost a round each.  Ties go to the smaller P (fewer partial sums to add).
+// From batch 5 on the vector form has the registers for one workgroup per CU only; k_down2_mfma has
+// room for two at any batch, but gains nothing from them there (steps of 6 layers, P = 2 / 4, us:
+// d 7168 batch 5 396 / 399, batch 8 424 / 428; d 8192 batch 5 359 / 364, batch 8 386 / 389).
 // two_per_cu = false: one round only (FC2 over segments, whose workgroups carry more state;
 // measured at the OPT-30B and Falcon-40B shapes at batch 2: 776 against 752, 638 against 628).
 inline int fc2_split(const pf_ctx *ctx, int tiles, int B, bool two_per_cu = true)
@@ -1762,7 +1767,7 @@ pf_status pf_ctx_set_option(pf_ctx *ctx, int key, int value)
         case PF_OPT_HIDDEN_MFMA_MIN_ELEMS:
             if (value < 0) break;
             ctx->hidden_mfma_min_elems = value;
-            ctx->hidden_mfma_min_elems_fc1 = ctx->hidden_mfma_min_elems_glue = value;
+            ctx->hidden_mfma_min_elems_one = ctx->hidden_mfma_min_elems_both = value;
             return PF_OK;
         case PF_OPT_UP_GRID:
             if (value < 0 || value > 65535) break;

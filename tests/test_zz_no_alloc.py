@@ -62,7 +62,7 @@ def test_noalloc_on_matrix_cores_same_bits_from_fp32_operands(pf):
 
 
 @pytest.mark.parametrize("act", [wl.ACT_RELU, wl.ACT_REGLU])
-@pytest.mark.parametrize("d,r,B", [(7168, 64, 3), (5184, 136, 4), (8192, 96, 4)])
+@pytest.mark.parametrize("d,r,B", [(7168, 64, 3), (4608, 64, 4), (5184, 136, 4), (8192, 96, 4)])
 def test_noalloc_on_matrix_cores_same_bits_ragged(pf, d, r, B, act):
     """The same with fewer tokens than columns kept for them, rows that end inside a chunk, and a
     hidden vector that the output layer takes as fp32 values (r no multiple of 32)."""
