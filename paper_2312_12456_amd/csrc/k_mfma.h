@@ -666,9 +666,9 @@ __global__ __launch_bounds__(kMfmaThreads) void k_rows_mfma(
 // Bound by memory: ids and h of the next chunk are requested in front of the rows of this one, so
 // a wave waits for one round trip per 8 KB.  126 registers leave room for two workgroups per CU
 // (the second launch of the look-ahead form needs that).
-// Vector form -> this one, us: OPT-30B shape batch 8 (65 MB) 21.9 -> 17.4, LLaMA-13B shape batch 4
-// (44 MB) 14.8 -> 12.3, all 16384 neurons of an OPT-6.7B layer at batch 4 (134 MB) 35.3 -> 25.7.
-// (The two-half form: 17.3, 11.9, 26.2.)
+// Vector form -> this one, us: OPT-30B shape batch 8 (65 MB) 21.0 -> 16.6, LLaMA-13B shape batch 4
+// (44 MB) 14.8 -> 12.0, all 16384 neurons of an OPT-6.7B layer at batch 4 (134 MB) 35.3 -> 25.7.
+// (With two halves of h: 0.4 us less at most.)
 constexpr int kDown2mRows = 64;                       // list slots per chunk (one wave)
 constexpr int kDown2mPitch = kDown2Cols + 4;          // floats per token row of the partial sums
 constexpr int kDown2mRedFloats = 2 * kDown2Waves * 8 * kDown2mPitch;

@@ -397,9 +397,9 @@ constexpr int kGlueThreads = 1024;
 // [B][d] halfs cost the consumers two loads per step of 64-byte pieces from every token's row:
 // at the OPT-30B shape, batch 8, the hidden layer's 192 workgroups touched four times as many
 // lines for activations as for weights.)  The writers pay for it, as the workgroups of 8 tokens, on
-// different XCDs, each write 16 bytes of every 128-byte line: k_glue takes 5.6 us where it took 5.1
-// for planes (that shape, batch 8 as batch 3; 4.5 without either, batch 8), with 8-byte and with
-// 16-byte stores alike.  The consumers gain 4.2 (hidden layer), 2.6 (FC1) and 0.9 us (output layer).
+// different XCDs, each write 16 bytes of every 128-byte line: k_glue takes 5.8 us where it took 5.1
+// for planes (that shape, batch 8; batch 4 5.5 and 5.0), with 8-byte and with 16-byte stores alike.
+// The consumers gain 4.1 (hidden layer), 2.6 (FC1) and 0.9 us (output layer) a layer.
 __device__ __forceinline__ size_t split_at(int hs, int b, int c)
 {
     return (size_t)(c >> 3) * (size_t)(16 * hs) + (size_t)(b * 8 + (c & 7));
