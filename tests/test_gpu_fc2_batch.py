@@ -1,5 +1,6 @@
 """FC2 over listed fp16 rows for batches, against plain torch in 64 bits.  Batches of 4 and more
-with d % 32 == 0 run it on the matrix cores, other widths (2056 here) on the vector units: list
+with d % 32 == 0 run it on the matrix cores (at batch 4 lists of more than 256 rows per row group, the
+shorter ones as the vector form does), other widths (2056 here) on the vector units: list
 lengths around the 64-slot chunks, lists of several chunks per wave, column counts that are no
 multiple of the 64-column tile, and FC1 outputs over ranges that 16-bit halves cannot hold.
 
