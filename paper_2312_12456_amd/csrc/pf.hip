@@ -335,12 +335,12 @@ inline bool pred_mfma(const pf_ctx *ctx, const pf_layer_desc &D, int K, int B, b
 }
 
 // Whether FC1's row length lets it run on the matrix cores: a multiple of 32, or with a formed input (see
-// above) where the kernel is no less accurate than the vector form (dense FFN against 64 bits, 1e-7, matrix
-// / vector: ungated 768 1.125 / 1.128, 1536 1.12 / 1.19, 7168 1.47 / 1.57; gated 1024 1.68 / 1.51, 1536
-// 1.71 / 1.63, 2048 1.69 / 1.72, 5120 2.21 / 2.26).
+// above) a length at which that is faster and no less accurate than the vector form (figures at up_mfma_passes).
+// Ungated, stack of 12 layers, us, vector / matrix: 1032 x 3264 batch 4 233 / 242, batch 6 272 / 271; 1544 x 4928 batch 4
+// 265 / 246, batch 8 361 / 264.
 inline bool up_mfma_width(const pf_layer_desc &D, bool formed)
 {
-    return D.d % 32 == 0 || (formed && (D.act == PF_ACT_RELU || D.d >= 2048));
+    return D.d % 32 == 0 || (formed && D.d >= (D.act == PF_ACT_RELU ? kHiddenFormedMinD : 2048));
 }
 
 // Whether FC1 over a predicted list runs on the matrix cores.
@@ -936,6 +936,11 @@ hipEvent_t la_event(pf_ctx *ctx, size_t i)
     return ctx->la_events[i];
 }
 
+// Look-ahead schedules whose FC1 is a launch of its own: a formed input of ragged width goes to the matrix cores
+// (up_mfma_width) above this B * d only.  Ungated, 12 layers, us, vector / matrix: 5 x 1416 282 / 298, 4 x 1544 281 /
+// 291, 5 x 1544 290 / 287, 6 x 1544 300 / 292, 4 x 2056 311 / 278.
+inline bool la_ragged_mfma(int d, int B) { return B * d > 8192; }
+
 // One decode step with look-ahead prediction at distance 1: the predictor of layer l reads
 // the input of layer l-1 (layer 0 and 1: the stack's input) and runs on the side stream
 // while the main stream is busy with the sparse kernels of layer l-1.  Masks alternate
@@ -971,7 +976,8 @@ pf_status stack_enqueue_lookahead(pf_ctx *ctx, pf_layer *const *layers, int n_la
         ctx->last_mask = masks[l & 1];
         ctx->last_idx = ctx->idx;
         ctx->last_count = ctx->count;
-        s = launch_sparse(ctx, layers[l], cur, B, nullptr, nullptr, masks[l & 1], nullptr, &ny, st, l > 0);
+        s = launch_sparse(ctx, layers[l], cur, B, nullptr, nullptr, masks[l & 1], nullptr, &ny, st,
+                          l > 0 && la_ragged_mfma(d, B));
         if (s == PF_OK) s = trace_mask(ctx, l, layers[l], masks[l & 1], false, st);
         if (s != PF_OK) return s;
         if (l + 1 < n_layers) {
@@ -1008,7 +1014,8 @@ pf_status stack_enqueue_lookahead_serial(pf_ctx *ctx, pf_layer *const *layers, i
         ctx->last_mask = masks[l & 1];
         ctx->last_idx = ctx->idx;
         ctx->last_count = ctx->count;
-        s = launch_sparse(ctx, layers[l], cur, B, nullptr, nullptr, masks[l & 1], nullptr, &ny, st, l > 0);
+        s = launch_sparse(ctx, layers[l], cur, B, nullptr, nullptr, masks[l & 1], nullptr, &ny, st,
+                          l > 0 && la_ragged_mfma(d, B));
         if (s == PF_OK) s = trace_mask(ctx, l, layers[l], masks[l & 1], false, st);
         if (s != PF_OK) return s;
         if (l + 1 < n_layers) {
