@@ -95,7 +95,9 @@ typedef struct pf_plan pf_plan;
  * pf_dense_ffn and the layer steps, the first x of a stack -- and the predictor's hidden vector must
  * lie inside the fp16 range (|x| < 65504), which normalised hidden states do by orders of
  * magnitude.  FC2 of such batches takes FC1's outputs with all of their bits and over all of
- * fp32's range.
+ * fp32's range.  An infinite fp16 weight of FC1, FC2 or the predictor's hidden layer gives the sum that
+ * fp32 arithmetic gives in every form; one of the predictor's output layer may give NaN on the matrix
+ * cores (the neuron is then not listed).
  *
  * Context: binds a device and owns scratch sized for the given maxima (hidden vector,
  * mask words, index list, FC1 outputs, FC2 partial sums).  `device` is a HIP ordinal.

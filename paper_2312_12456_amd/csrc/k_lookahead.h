@@ -147,7 +147,8 @@ __global__ __launch_bounds__(kMfmaThreads) void k_la_up_hidden_mfma(
     const __half *__restrict__ w_up, const __half *__restrict__ w_gate,
     const float *__restrict__ b_up, const void *__restrict__ xs, int B,
     const uint64_t *__restrict__ mask_words, int32_t *__restrict__ idx_out,
-    int32_t *__restrict__ count_out, float *__restrict__ h, int hs, int d, int ffn, float up_floor)
+    int32_t *__restrict__ count_out, float *__restrict__ h, int hs, int d, int ffn, float up_floor,
+    const float *__restrict__ x)
 {
     extern __shared__ uint64_t dyn_lds64[];
     __shared__ int irow[32];
@@ -155,10 +156,10 @@ __global__ __launch_bounds__(kMfmaThreads) void k_la_up_hidden_mfma(
     __shared__ float logit_s[16][16];
     const int n_up = (int)gridDim.x - n_hid, bid = (int)blockIdx.x;
     if (bid < n_up) {  // uniform over the block
-        up_mfma_body<ACT, true, true>(dyn_lds64, irow, brow, bid, n_up, w_up, w_gate, b_up, xs, B,
+        up_mfma_body<ACT, true, true>(dyn_lds64, irow, brow, bid, n_up, w_up, w_gate, b_up, xs, x, B,
                                       nullptr, nullptr, mask_words, idx_out, count_out, h, hs, d, ffn, up_floor);
     } else {
-        rows_mfma_body<8, 512, 0, true>(dyn_lds64, logit_s, bid - n_up, p1, xs, B, d, r, nullptr, 0.f, nullptr,
+        rows_mfma_body<8, 512, 0, true>(dyn_lds64, logit_s, bid - n_up, p1, xs, x, B, d, r, nullptr, 0.f, nullptr,
                                         nullptr, 0, t_split);
     }
 }
@@ -183,7 +184,7 @@ __global__ __launch_bounds__(kMfmaThreads, 4) void k_la_down_out_mfma(
         down2_mfma_body(reinterpret_cast<float *>(dyn_lds64), bid % tiles, bid / tiles, P, w_down, b_down,
                         h, idx, count_p, part, B, hs, d, ffn);
     } else {
-        rows_mfma_body<64, 64, 1, true>(dyn_lds64, logit_s, bid - n_fc2, p2, t_split, B, r, ffn_next, p_bias,
+        rows_mfma_body<64, 64, 1, true>(dyn_lds64, logit_s, bid - n_fc2, p2, t_split, nullptr, B, r, ffn_next, p_bias,
                                         thr_logit, nullptr, mask_next, first_word);
     }
 }

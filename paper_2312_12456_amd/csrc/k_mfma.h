@@ -139,6 +139,22 @@ __device__ __forceinline__ float get_tile(const float *ct, int e, int el)  // el
     return XS ? fmaf(ct[el], kSplitLo, ct[e]) : ct[e];
 }
 
+// One row of w (at byte row_off) times token b of the fp32 activations x, by a wave.  For sums that came out NaN
+// on the matrix cores: an infinite weight has met a half that is zero, or halves of both signs, where x itself
+// gives an infinite sum.  (Where x gives NaN too, this does.)  Never taken with finite weights and activations.
+__device__ __forceinline__ float row_sum_f32(rsrc_t w, uint32_t row_off, rsrc_t x, int b, int K, int lane)
+{
+    float s = 0.f;
+#pragma unroll 1
+    for (int k0 = 0; k0 < K; k0 += kChunk) {
+        const int k = k0 + lane * 8;
+        const uint32_t at = k < K ? (uint32_t)(b * K + k) * 4u : kOobOffset;
+        const uint4 q = ld16_cached(w, k < K ? row_off + (uint32_t)k * 2u : kOobOffset);
+        s = dot8(q, ld16_f32(x, at), ld16_f32(x, k < K ? at + 16u : kOobOffset), s);
+    }
+    return wave_sum(s);
+}
+
 // Put chunk `c` (KC = 4096 / R elements) of the R rows of a pass in flight towards `slot`.  One
 // instruction moves 1 KB: 2 KC bytes (whole lines) of each of 512 / KC rows.  Row r stores
 // 16-byte piece p at position p ^ (r & 7), so that the 8 rows a group of 8 lanes reads together
@@ -162,7 +178,7 @@ __device__ __forceinline__ void mfma_issue_chunk(rsrc_t w, char *slot, const uin
 
 // What the passes of a block need from the kernel around them.
 struct UpMfmaArgs {
-    rsrc_t wu, wg, xr;
+    rsrc_t wu, wg, xr, xf;  // xr: the activations as the matrix cores take them; xf: in fp32
     const float *b_up;
     const int32_t *idx_in;
     int32_t *idx_out;
@@ -331,9 +347,22 @@ __device__ __forceinline__ void up_mfma_passes(const UpMfmaArgs &a)
                     pu[wv] += pu[wv + o];
                     pg[wv] += pg[wv + o];
                 }
-            const float su = pu[0], sg = pg[0];
+            float su = pu[0], sg = pg[0];
             const int i = a.irow[row];
             const int j = j0 + row;
+            // wave by wave (T * 256 is whole waves)
+            uint64_t again = __ballot(colb < a.B && j < a.j_end && i >= 0 && (su != su || sg != sg));
+            for (; __builtin_expect(again != 0, 0); again &= again - 1) {
+                const int l = (int)__builtin_ctzll(again);
+                const uint32_t off = (uint32_t)__builtin_amdgcn_readlane(i, l) * (uint32_t)d * 2u;
+                const int b = __builtin_amdgcn_readlane(colb, l);
+                const float u = row_sum_f32(a.wu, off, a.xf, b, d, lane);
+                const float g = GATED ? row_sum_f32(a.wg, off, a.xf, b, d, lane) : 0.f;
+                if (lane == l) {
+                    su = u;
+                    sg = g;
+                }
+            }
             const float bias = a.brow[row];  // fetched when the row was selected
             const float v = GATED ? fmaxf(sg + bias, 0.f) * fmaxf(su, a.up_floor) : fmaxf(su + bias, 0.f);
             if (colb < a.B && j < a.j_end) a.h[(size_t)j * a.hs + colb] = i >= 0 ? v : 0.f;
@@ -360,12 +389,12 @@ __device__ __forceinline__ void up_mfma_passes(const UpMfmaArgs &a)
 // wrote, and the wait between the two is the compiler's, which places it only while it takes
 // the two accesses to alias.  Inlining a function with restrict parameters tags its accesses
 // with no-alias scopes, and with those the waits were dropped (wrong sums on the device).
-// XS: x points at the split halves of the activations (see XRaw) instead of fp32 values.
+// XS: x points at the split halves of the activations (see XRaw) instead of fp32 values.  xf: the fp32 values.
 template <int ACT, bool FROM_MASK, bool XS>
 __device__ __forceinline__ void up_mfma_body(
     uint64_t *dyn_lds64, int *irow, float *brow, const int bid, const int nblocks,
     const __half *w_up, const __half *w_gate,
-    const float *b_up, const void *x, int B,
+    const float *b_up, const void *x, const float *xf, int B,
     const int32_t *idx_in, const int32_t *count_in,
     const uint64_t *mask_words, int32_t *idx_out,
     int32_t *count_out, float *h, int hs, int d, int ffn, float up_floor)
@@ -391,6 +420,7 @@ __device__ __forceinline__ void up_mfma_body(
     a.wu = make_rsrc(w_up, (uint32_t)ffn * (uint32_t)d * 2u);
     a.wg = make_rsrc(GATED ? w_gate : w_up, (uint32_t)ffn * (uint32_t)d * 2u);
     a.xr = make_rsrc(x, x_bytes<XS>(B, d));
+    a.xf = make_rsrc(xf, x_bytes<false>(B, d));
     a.b_up = b_up;
     a.idx_in = idx_in;
     a.idx_out = idx_out;
@@ -426,13 +456,14 @@ __global__ __launch_bounds__(kMfmaThreads) void k_up_mfma(
     const float *__restrict__ b_up, const void *__restrict__ x, int B,
     const int32_t *__restrict__ idx_in, const int32_t *__restrict__ count_in,
     const uint64_t *__restrict__ mask_words, int32_t *__restrict__ idx_out,
-    int32_t *__restrict__ count_out, float *__restrict__ h, int hs, int d, int ffn, float up_floor)
+    int32_t *__restrict__ count_out, float *__restrict__ h, int hs, int d, int ffn, float up_floor,
+    const float *__restrict__ xf)
 {
     extern __shared__ uint64_t dyn_lds64[];
     __shared__ int irow[32];
     __shared__ float brow[32];
     up_mfma_body<ACT, FROM_MASK, XS>(dyn_lds64, irow, brow, (int)blockIdx.x, (int)gridDim.x, w_up, w_gate,
-                                 b_up, x, B, idx_in, count_in, mask_words, idx_out, count_out, h, hs, d,
+                                 b_up, x, xf, B, idx_in, count_in, mask_words, idx_out, count_out, h, hs, d,
                                  ffn, up_floor);
 }
 
@@ -471,13 +502,13 @@ __device__ __forceinline__ void rows_mfma_issue(rsrc_t w, char *slot, uint32_t r
 
 // Body: bid0 = the block's number within its role, logit_s = [16][16 * tiles] floats of LDS.
 // No restrict qualifiers, for the same reason as in up_mfma_body.
-// XS: v points at the split halves of the activations (see XRaw) instead of fp32 values.
+// XS: v points at the split halves of the activations (see XRaw) instead of fp32 values.  vf (EPI 0): the fp32 values.
 // out_split (EPI 0; may be null): the hidden vector goes there as split halves, the form in which
 // the output layer's matrix-core kernel takes it, instead of to out.
 template <int R, int KC, int EPI, bool XS>
 __device__ __forceinline__ void rows_mfma_body(
     uint64_t *dyn_lds64, float (*logit_s)[16 * ((R + 15) / 16)], const int bid0,
-    const __half *w, const void *v, int B, int K, int nrows,
+    const __half *w, const void *v, const float *vf, int B, int K, int nrows,
     const float *p_bias, float thr_logit, float *out,
     uint64_t *mask_words, int first_word, __half *out_split = nullptr)
 {
@@ -610,8 +641,16 @@ __device__ __forceinline__ void rows_mfma_body(
         for (int o = kMfmaWaves / 2; o >= 1; o /= 2)
 #pragma unroll
             for (int wv = 0; wv < o; ++wv) s[wv] += s[wv + o];
-        const float sum = s[0];
+        float sum = s[0];
         if (EPI == 0) {
+            const rsrc_t fr = make_rsrc(vf, x_bytes<false>(B, K));
+            uint64_t again = __ballot(col < B && row < R && row < nleft && sum != sum);
+            for (; __builtin_expect(again != 0, 0); again &= again - 1) {  // wave by wave (T * 256 is whole waves)
+                const int l = (int)__builtin_ctzll(again);
+                const float u = row_sum_f32(wr, row0_off + (uint32_t)__builtin_amdgcn_readlane(row, l) * row_bytes, fr,
+                                            __builtin_amdgcn_readlane(col, l), K, lane);
+                if (lane == l) sum = u;
+            }
             if (col < B && row < R && row < nleft) {
                 const float o = fmaxf(sum, 0.f);
                 if (out_split != nullptr) {
@@ -642,12 +681,14 @@ __device__ __forceinline__ void rows_mfma_body(
     PF_TSTAMP(EPI, 2);
 }
 
+// (vf, and xf of FC1's kernels, come last: in front they pushed arguments that are needed at once into another line,
+// 0.3 us a launch.)
 template <int R, int KC, int EPI, bool XS>
 __global__ __launch_bounds__(kMfmaThreads) void k_rows_mfma(
     const __half *__restrict__ w, const void *__restrict__ v, int B, int K, int nrows,
     const float *__restrict__ p_bias, float thr_logit, float *__restrict__ out,
     uint64_t *__restrict__ mask_words, int first_word, const int32_t *__restrict__ skip,
-    __half *__restrict__ out_split)
+    __half *__restrict__ out_split, const float *__restrict__ vf)
 {
     extern __shared__ uint64_t dyn_lds64[];
     constexpr int T = (R + 15) / 16;
@@ -661,7 +702,7 @@ __global__ __launch_bounds__(kMfmaThreads) void k_rows_mfma(
         }
         return;
     }
-    rows_mfma_body<R, KC, EPI, XS>(dyn_lds64, logit_s, (int)blockIdx.x, w, v, B, K, nrows, p_bias, thr_logit,
+    rows_mfma_body<R, KC, EPI, XS>(dyn_lds64, logit_s, (int)blockIdx.x, w, v, vf, B, K, nrows, p_bias, thr_logit,
                                out, mask_words, first_word, out_split);
 }
 

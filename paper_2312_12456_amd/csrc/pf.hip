@@ -392,11 +392,11 @@ pf_status launch_hidden(pf_ctx *ctx, const pf_layer *L, const float *x, const fl
         if (xs)
             PF_LAUNCH(ps, (pf::k_rows_mfma<8, 512, 0, true>), dim3(cdiv(D.r, 8)), dim3(pf::kMfmaThreads),
                       (size_t)pf::kMfmaWaves * pf::kRowsMfmaSlotBytes, st, p1, (const void *)xs, B, D.d, D.r,
-                      (const float *)nullptr, 0.f, ctx->t, (uint64_t *)nullptr, 0, skip, ts);
+                      (const float *)nullptr, 0.f, ctx->t, (uint64_t *)nullptr, 0, skip, ts, x);
         else
             PF_LAUNCH(ps, (pf::k_rows_mfma<8, 512, 0, false>), dim3(cdiv(D.r, 8)), dim3(pf::kMfmaThreads),
                       (size_t)pf::kMfmaWaves * pf::kRowsMfmaSlotBytes, st, p1, (const void *)x, B, D.d, D.r,
-                      (const float *)nullptr, 0.f, ctx->t, (uint64_t *)nullptr, 0, skip, ts);
+                      (const float *)nullptr, 0.f, ctx->t, (uint64_t *)nullptr, 0, skip, ts, x);
         PF_HIP(ctx, hipGetLastError());
         return PF_OK;
     }
@@ -476,7 +476,8 @@ pf_status launch_predict(pf_ctx *ctx, const pf_layer *L, const float *x, const f
 #define PF_OUTM(XSV, V)                                                                             \
     PF_LAUNCH(ps, (pf::k_rows_mfma<64, 64, 1, XSV>), dim3(pred_out_words(L)), dim3(pf::kMfmaThreads), \
               (size_t)pf::kMfmaWaves * pf::kRowsMfmaSlotBytes, st, p2, (const void *)(V), B, D.r, D.ffn, \
-              L->w.p_bias, L->thr_logit, scores, mask_words, L->always_on / 64, skip, (__half *)nullptr)
+              L->w.p_bias, L->thr_logit, scores, mask_words, L->always_on / 64, skip, (__half *)nullptr, \
+              (const float *)nullptr)
         if (ctx->t_split)
             PF_OUTM(true, ctx->tsplit);
         else
@@ -646,7 +647,7 @@ pf_status launch_sparse(pf_ctx *ctx, const pf_layer *L, const float *x, int B,
 #define PF_UPM(ACT, FM, XSV)                                                                          \
     PF_LAUNCH(ps, (pf::k_up_mfma<ACT, FM, XSV>), dim3(grid), dim3(pf::kMfmaThreads), mfma_lds, st, w_up, \
               w_gate, L->w.b_up, xop, B, idx_in, count_in, mask_words, ctx->idx, ctx->count, ctx->h,   \
-              pf::h_stride(B), D.d, D.ffn, up_floor_of(D))
+              pf::h_stride(B), D.d, D.ffn, up_floor_of(D), x)
         if (xs && gated) { PF_UPM(1, true, true); }
         else if (xs) { PF_UPM(0, true, true); }
         else if (gated && from_mask) { PF_UPM(1, true, false); }
@@ -1223,7 +1224,7 @@ pf_status stack_enqueue_lookahead_merged_mfma(pf_ctx *ctx, pf_layer *const *laye
               static_cast<const __half *>(L->w.w_up), static_cast<const __half *>(L->w.w_gate),        \
               L->w.b_up, (const void *)xs, B, (const uint64_t *)masks[l & 1], ctx->idx, ctx->count,    \
               ctx->h,                                                                                  \
-              pf::h_stride(B), D.d, D.ffn, up_floor_of(D))
+              pf::h_stride(B), D.d, D.ffn, up_floor_of(D), cur)
             if (gated)
                 PF_LA1M(1);
             else
