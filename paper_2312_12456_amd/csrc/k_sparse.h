@@ -103,10 +103,13 @@ __device__ __forceinline__ void up_body(
     PF_TSTAMP(2, 5);
     WGroup<U> gu, gg;
     rsrc_t ru = row_rsrc(w_up, i, d, valid), rg = row_rsrc(GATED ? w_gate : w_up, i, d, valid);
+    // The first row's bias is requested in front of its weights and kept as a scalar: behind the sums it was a trip to
+    // HBM of its own.  Those of later rows are scalar loads behind their sums, which other waves' work hides; as
+    // vector loads beside the next row's weights they cost lists of many rows a wave 4 - 6 % (pf_dense_ffn of 7176 x
+    // 22912 at batch 8, FC1 alone 122 / 130 us).
+    const float bias_first = ld4_f32(bias_rsrc(b_up, ffn), valid ? (uint32_t)i * 4u : kOobOffset);
     load_group<U>(gu, ru, 0, lane);
     if (GATED) load_group<U>(gg, rg, 0, lane);
-    const rsrc_t br = bias_rsrc(b_up, ffn);
-    float bias = ld4_f32(br, valid ? (uint32_t)i * 4u : kOobOffset);
 
     PF_TSTAMP(2, 2);
     float scale[B];
@@ -149,6 +152,8 @@ __device__ __forceinline__ void up_body(
         for (int b = 0; b < B; ++b) scale[b] = 1.f;
     }
     PF_TSTAMP(2, 3);
+    const float bias0 = lane_value(bias_first, 0);
+    bool first = true;
 
     while (j < n) {  // wave-uniform; no block-level synchronisation inside
         float au[B], ag[B];
@@ -162,9 +167,8 @@ __device__ __forceinline__ void up_body(
             fma_group<B, U>(gu, xs, kpad, it0, nch, lane, au);
             if (GATED) fma_group<B, U>(gg, xs, kpad, it0, nch, lane, ag);
         }
-        const int jcur = j;
+        const int jcur = j, icur = i;
         const bool vcur = valid;
-        const float bcur = bias;
         j += stride;
         if (j < n) {  // next row in flight before this row's reductions
             i = wave_uniform(neuron_of(j));
@@ -174,8 +178,9 @@ __device__ __forceinline__ void up_body(
             rg = row_rsrc(GATED ? w_gate : w_up, i, d, valid);
             load_group<U>(gu, ru, 0, lane);
             if (GATED) load_group<U>(gg, rg, 0, lane);
-            bias = ld4_f32(br, valid ? (uint32_t)i * 4u : kOobOffset);
         }
+        const float bcur = first ? bias0 : (b_up != nullptr && vcur) ? b_up[icur] : 0.f;
+        first = false;
 #pragma unroll
         for (int b = 0; b < B; ++b) {
             float v;
@@ -590,20 +595,21 @@ __device__ __forceinline__ void down2_body(
 
     int n = 0;
     bool have_n = false;
-    float bpre = 0.f;
     for (int r0 = 0; r0 == 0 || r0 * P < n; r0 += kDown2RowsPerLoad * U) {
         Down2Round<B> r;
         down2_request<B>(r, r0, rslot, g, P, h, idx, ffn);
         if (!have_n) {
             n = min(max(*count_p, 0), ffn);
             have_n = true;
-            bpre = down2_bias(b_down, tile, g, d);
             PF_TSTAMP(3, 1);
         }
         down2_round<B>(acc, r, wd, r0, rslot, g, P, col, n, d, ffn);
         if (r0 == 0) PF_TSTAMP(3, 2);
     }
     PF_TSTAMP(3, 3);
+    // requested here, under the lane sums: held through the loop it cost lists of several rounds 7 % (2056 x 6528 dense
+    // batch 4, 15.2 / 16.4 us)
+    const float bpre = down2_bias(b_down, tile, g, d);
     down2_finish<B>(acc, red, tile, g, bpre, part, d);
     PF_TSTAMP(3, 5);
 }
