@@ -58,10 +58,15 @@ __global__ __launch_bounds__(kUpThreads) void k_la_up_hidden(
 // per wave).  grid = n_up + ceil(r / hid_rows), block = 64 * cols_waves(d): FC1's blocks have the low
 // numbers.  Dynamic LDS: up_cols_lds_bytes.  Two workgroups fit a CU, one of either role: at most 128
 // registers up to two chunks per wave, and hid_rows (2, 4 or la_hid_rows_max) rows of the hidden layer per block.
+// No scratch memory: the glue is formed token by token, the hidden layer's body knows that one pass covers the
+// row, and where two tokens meet two chunks a wave there are at most 4 rows of the hidden layer and, gated, one
+// row of FC1 at a time.  (All tokens at once, 6 and 2 rows: up to 162 registers in scratch and, us, 8192 x 26176
+// batch 2 (4 layers) 242 against 213 now, gated 7168 x 22912 batch 2 (4) 240 / 210, 3072 x 9792, r 1536 batch 3 (12)
+// 337 / 261, 4096 x 13056, r 2048 batch 3 (7) 246 / 205.)
 // One wave per row with x in LDS -> this, and the second launch with two workgroups per CU, a step of the stack,
 // us: 30B-class batch 1 (8 layers) 303 -> 263, batch 2 387 -> 342, 13B-class gated (12) 331 -> 305, 7B-class batch 1
 // 563 -> 548, batch 2 (12) 285 -> 255, 3000 x 9600 batch 2 (8) 153 -> 132.
-constexpr __host__ __device__ int la_hid_rows_max(int B, int cpw) { return B == 3 || cpw == 3 ? 4 : 6; }
+constexpr __host__ __device__ int la_hid_rows_max(int B, int cpw) { return B * cpw >= 3 ? 4 : 6; }
 
 template <int B, int ACT, bool GLUE, int CPW>
 __global__ __launch_bounds__(64 * kColsMaxWaves) __attribute__((amdgpu_waves_per_eu(CPW <= 2 ? 4 : 2, 4))) void
@@ -74,7 +79,8 @@ k_la_up_hidden_cols(
     extern __shared__ __align__(16) char cols_lds[];
     const int bid = (int)blockIdx.x;
     if (bid < n_up) {  // uniform over the block
-        up_cols_body<B, ACT, true, GLUE, CPW, UpColsR<B, ACT, CPW>::value, (CPW * B > 2)>(
+        constexpr int R = B == 2 && CPW == 2 && ACT == 1 ? 1 : UpColsR<B, ACT, CPW>::value;
+        up_cols_body<B, ACT, true, GLUE, CPW, R, (CPW * B > 2), 1>(
             cols_lds, bid, n_up, bid == 0, w_up, w_gate, b_up, x, gi, x_new, nullptr, nullptr, mask_words, idx_out,
             count_out, h, hs, d, ffn, up_floor);
     } else {
@@ -82,7 +88,7 @@ k_la_up_hidden_cols(
         static_assert(RED <= kUpColsRows * kColsMaxWaves, "the hidden layer's sums fit FC1's LDS");
         float *xch = reinterpret_cast<float *>(cols_lds);
         auto hidden = [&](auto rows) {
-            hidden_cols_body<B, GLUE, CPW, decltype(rows)::value, (CPW * B > 2)>(
+            hidden_cols_body<B, GLUE, CPW, decltype(rows)::value, (CPW * B > 2), 1, true>(
                 xch + (blockDim.x >> 6) * kColsXFloats, xch + (threadIdx.x >> 6) * kColsXFloats, bid - n_up, false, p1,
                 x, gi, nullptr, t, d, r);
         };

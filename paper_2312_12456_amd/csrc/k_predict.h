@@ -4,8 +4,10 @@
 //   output : logit[b][i] = p2[i] . t[b] + p_bias[i]                     ffn rows of r fp16
 //            bit i of the mask = any_b(logit[b][i] > logit(threshold))  (wave ballot)
 //   compact: idx[] = ascending positions of the set bits, count = popcount
-// Both GEMVs are HBM-bound streams of fp16 rows: one wave per row, 16-byte loads per
-// lane, activations staged once per workgroup in LDS, fp32 accumulation, DPP reduction.
+// Both GEMVs are HBM-bound streams of fp16 rows, 16-byte loads per lane, fp32 accumulation.  Two forms:
+// batch 1 .. 3 holds the activations by column in registers (hidden_cols_body, pred_out_cols_body); rows longer
+// than that covers, and batches of 4 to 8 below the matrix cores' line, take one wave per row with the
+// activations staged once per workgroup in LDS and a DPP reduction (pred_hidden_body, pred_out_body).
 // No kernel here uses device-scope fences: data crosses workgroups only at kernel ends.
 #pragma once
 #include "dev_util.h"
@@ -253,24 +255,26 @@ struct ColGlue {
     uint32_t slo[B], shi[B];
 };
 
-template <int B, int NY>
-__device__ __forceinline__ void colglue_issue(ColGlue<B, NY> &g, rsrc_t xr, rsrc_t yr, rsrc_t sr, uint32_t sstride,
+// Tokens T0 .. T0 + N - 1.
+template <int N, int NY, int T0 = 0>
+__device__ __forceinline__ void colglue_issue(ColGlue<N, NY> &g, rsrc_t xr, rsrc_t yr, rsrc_t sr, uint32_t sstride,
                                               uint32_t pbytes, int e, int d)
 {
     const bool ok = e < d, ok2 = e + 256 < d;
 #pragma unroll
-    for (int b = 0; b < B; ++b) {
+    for (int i = 0; i < N; ++i) {
+        const int b = T0 + i;
         const uint32_t off = (uint32_t)(b * d + e) * 4u, soff = (uint32_t)b * sstride + ((uint32_t)e >> 3);
-        g.lo[b][NY] = ld16_f32(xr, ok ? off : kOobOffset);
-        g.hi[b][NY] = ld16_f32(xr, ok2 ? off + 1024u : kOobOffset);
+        g.lo[i][NY] = ld16_f32(xr, ok ? off : kOobOffset);
+        g.hi[i][NY] = ld16_f32(xr, ok2 ? off + 1024u : kOobOffset);
 #pragma unroll
         for (int p = 0; p < NY; ++p) {
-            g.lo[b][p] = ld16_f32(yr, ok ? off + (uint32_t)p * pbytes : kOobOffset);
-            g.hi[b][p] = ld16_f32(yr, ok2 ? off + (uint32_t)p * pbytes + 1024u : kOobOffset);
+            g.lo[i][p] = ld16_f32(yr, ok ? off + (uint32_t)p * pbytes : kOobOffset);
+            g.hi[i][p] = ld16_f32(yr, ok2 ? off + (uint32_t)p * pbytes + 1024u : kOobOffset);
         }
         if (b > 0) {  // row 0 keeps its signs
-            g.slo[b] = __builtin_amdgcn_raw_buffer_load_b8(sr, (int)(ok ? soff : kOobOffset), 0, 0);
-            g.shi[b] = __builtin_amdgcn_raw_buffer_load_b8(sr, (int)(ok2 ? soff + 32u : kOobOffset), 0, 0);
+            g.slo[i] = __builtin_amdgcn_raw_buffer_load_b8(sr, (int)(ok ? soff : kOobOffset), 0, 0);
+            g.shi[i] = __builtin_amdgcn_raw_buffer_load_b8(sr, (int)(ok2 ? soff + 32u : kOobOffset), 0, 0);
         }
     }
 }
@@ -283,8 +287,8 @@ __device__ __forceinline__ float4 with_signs(const float4 &v, uint32_t bits)
     return make_float4(one(v.x, 0), one(v.y, 1), one(v.z, 2), one(v.w, 3));
 }
 
-template <int B, int NY>
-__device__ __forceinline__ void colglue_commit(const ColGlue<B, NY> &g, ColX<B> &v, float *ss, int lane)
+template <int B, int N, int NY, int T0 = 0>
+__device__ __forceinline__ void colglue_commit(const ColGlue<N, NY> &g, ColX<B> &v, float *ss, int lane)
 {
     auto sum4 = [&](const float4 (&q)[NY + 1]) {
         float4 c = q[0];
@@ -294,16 +298,32 @@ __device__ __forceinline__ void colglue_commit(const ColGlue<B, NY> &g, ColX<B> 
     };
     const int sh = (lane & 1) * 4;  // e & 4
 #pragma unroll
-    for (int b = 0; b < B; ++b) {
-        float4 a = sum4(g.lo[b]), c = sum4(g.hi[b]);
+    for (int i = 0; i < N; ++i) {
+        const int b = T0 + i;
+        float4 a = sum4(g.lo[i]), c = sum4(g.hi[i]);
         if (b > 0) {
-            a = with_signs(a, g.slo[b] >> sh);
-            c = with_signs(c, g.shi[b] >> sh);
+            a = with_signs(a, g.slo[i] >> sh);
+            c = with_signs(c, g.shi[i] >> sh);
         }
         ss[b] = fmaf(a.x, a.x, fmaf(a.y, a.y, fmaf(a.z, a.z, fmaf(a.w, a.w, ss[b]))));
         ss[b] = fmaf(c.x, c.x, fmaf(c.y, c.y, fmaf(c.z, c.z, fmaf(c.w, c.w, ss[b]))));
         v.lo[b] = a;
         v.hi[b] = c;
+    }
+}
+
+// One chunk's glue for all tokens, N of them at a time (the rest of B last).
+template <int B, int NY, int N, int T0 = 0>
+__device__ __forceinline__ void colglue_chunk(ColX<B> &v, float *ss, rsrc_t xr, rsrc_t yr, rsrc_t sr, uint32_t sstride,
+                                              uint32_t pbytes, int e, int d, int lane)
+{
+    if constexpr (T0 < B) {
+        constexpr int M = B - T0 < N ? B - T0 : N;
+        ColGlue<M, NY> g;
+        colglue_issue<M, NY, T0>(g, xr, yr, sr, sstride, pbytes, e, d);
+        colglue_commit<B, M, NY, T0>(g, v, ss, lane);
+        __builtin_amdgcn_sched_barrier(0);
+        colglue_chunk<B, NY, N, T0 + M>(v, ss, xr, yr, sr, sstride, pbytes, e, d, lane);
     }
 }
 
@@ -328,7 +348,8 @@ struct GlueIn {
 // Bound by the glue's bytes through each workgroup's memory path and one trip to memory.  One wave per row
 // with x staged in LDS -> this, us (glue included): d 5120, r 1024 batch 1 6.7 -> 5.3; d 7168, r 1536 9.0 ->
 // 7.5; d 12288, r 2048 15.0 -> 12.5; d 4096, r 1024 batch 1 4.2 -> 4.4 (the stack 0.5 % faster), batch 3 8.5 ->
-// 7.6; only at d = 768 it is behind, 3.8 -> 4.4 (batch 2; at batch 1 0.8 % ahead).
+// 7.6.  Inside a stack it is behind at d = 768 batch 2, 3.8 -> 4.4 (the stack 15 % faster all the same), and at
+// d 4096, r 1024 batch 1 a trace had 4.2 -> 4.6.
 __host__ __device__ constexpr int cols_red_floats(int n) { return (n + 3) / 4 * 4; }
 
 // Sum of one value of the W <= MAX waves, `pitch` floats apart: all reads in flight at once.
@@ -344,8 +365,8 @@ __device__ __forceinline__ float cols_total(const float *p, int pitch, int W)
     return a;
 }
 
-// SEQ: chunks and tokens of the glue one after the other, for fewer registers.
-template <int B, bool GLUE, int CPW, int R, bool SEQ = (CPW * B > 3)>
+// SEQ: the glue chunk by chunk and GT tokens at a time, for fewer registers.  ONE: d <= 512 CPW waves, one pass.
+template <int B, bool GLUE, int CPW, int R, bool SEQ = (CPW * B > 3), int GT = B, bool ONE = false>
 __device__ __forceinline__ void hidden_cols_body(float *red, float *xw, const int bid, const bool write_x,
                                                  const __half *__restrict__ p1, const float *__restrict__ x,
                                                  const GlueIn gi, float *__restrict__ x_new,
@@ -386,22 +407,19 @@ __device__ __forceinline__ void hidden_cols_body(float *red, float *xw, const in
             // the address unit as much as any
             auto piece = [&](auto nyc) {
                 constexpr int NY = decltype(nyc)::value;
-                ColGlue<B, NY> g[CPW];
-                if (!SEQ) {
+                if constexpr (!SEQ) {
+                    ColGlue<B, NY> g[CPW];
 #pragma unroll
                     for (int c = 0; c < CPW; ++c)
                         colglue_issue<B, NY>(g[c], xr, yr, sr, (uint32_t)gi.sstride, pbytes, e0[c], d);
                     load_rows();  // queue up behind the activations
 #pragma unroll
-                    for (int c = 0; c < CPW; ++c) colglue_commit<B, NY>(g[c], v[c], acc + R * B, lane);
+                    for (int c = 0; c < CPW; ++c) colglue_commit(g[c], v[c], acc + R * B, lane);
                 } else {  // not enough registers for all of them at once
                     load_rows();
 #pragma unroll
-                    for (int c = 0; c < CPW; ++c) {
-                        colglue_issue<B, NY>(g[c], xr, yr, sr, (uint32_t)gi.sstride, pbytes, e0[c], d);
-                        colglue_commit<B, NY>(g[c], v[c], acc + R * B, lane);
-                        __builtin_amdgcn_sched_barrier(0);
-                    }
+                    for (int c = 0; c < CPW; ++c)
+                        colglue_chunk<B, NY, GT>(v[c], acc + R * B, xr, yr, sr, (uint32_t)gi.sstride, pbytes, e0[c], d, lane);
                 }
             };
             if (gi.ny == 4) piece(IntC<4>());
@@ -412,7 +430,7 @@ __device__ __forceinline__ void hidden_cols_body(float *red, float *xw, const in
             for (int c = 0; c < CPW; ++c)
 #pragma unroll
                 for (int b = 0; b < B; ++b) cols_exchange(xw, v[c].lo[b], v[c].hi[b], lane);
-            if (write_x && nch > step) {  // scaled in place below
+            if (!ONE && write_x && nch > step) {  // scaled in place below
 #pragma unroll
                 for (int c = 0; c < CPW; ++c)
                     if (col[c] < d)
@@ -438,6 +456,7 @@ __device__ __forceinline__ void hidden_cols_body(float *red, float *xw, const in
 #pragma unroll
                 for (int b = 0; b < B; ++b)
                     acc[q * B + b] = dot8(w[c][q], v[c].lo[b], v[c].hi[b], acc[q * B + b]);
+        if (ONE) break;
     }
     float s[NP / 4];
     wave_sums<N>(acc, s);
@@ -460,13 +479,14 @@ __device__ __forceinline__ void hidden_cols_body(float *red, float *xw, const in
 #pragma unroll
         for (int b = 0; b < B; ++b) {
             const float sc = scale_of(b);
-            for (int c0 = 0; c0 < nch; c0 += step)
+            for (int c0 = 0; c0 < (ONE ? 1 : nch); c0 += step)
 #pragma unroll
                 for (int c = 0; c < CPW; ++c) {
                     const int col = ((c0 + c * W + wave) * 64 + lane) * 8;
                     if (col >= d) continue;
                     float4 *to = reinterpret_cast<float4 *>(x_new + (size_t)b * d + col);
-                    const float4 a = nch > step ? to[0] : v[c].lo[b], e = nch > step ? to[1] : v[c].hi[b];
+                    const bool again = !ONE && nch > step;
+                    const float4 a = again ? to[0] : v[c].lo[b], e = again ? to[1] : v[c].hi[b];
                     to[0] = make_float4(a.x * sc, a.y * sc, a.z * sc, a.w * sc);
                     to[1] = make_float4(e.x * sc, e.y * sc, e.z * sc, e.w * sc);
                 }
@@ -483,7 +503,8 @@ __global__ __launch_bounds__(64 * kColsMaxWaves) __attribute__((amdgpu_waves_per
     __shared__ __align__(16) float xch[kColsMaxWaves * kColsXFloats];
     // adaptive layer step: a set flag means this step runs dense and needs no prediction
     if (skip != nullptr && *skip != 0) return;
-    hidden_cols_body<B, GLUE, CPW, R>(red, xch + (threadIdx.x >> 6) * kColsXFloats, (int)blockIdx.x, blockIdx.x == 0, p1, x, gi, x_new, t, d, r);
+    // (two tokens of rows longer than 8192 take two passes)
+    hidden_cols_body<B, GLUE, CPW, R, (CPW * B > 3), B, !(B == 2 && CPW == 2)>(red, xch + (threadIdx.x >> 6) * kColsXFloats, (int)blockIdx.x, blockIdx.x == 0, p1, x, gi, x_new, t, d, r);
 }
 
 // ---------------------------------------------------------------------------------------

@@ -223,18 +223,13 @@ __global__ __launch_bounds__(kUpThreads) void k_up(
 // batch 1 (the whole call within 1 %).
 constexpr int kUpColsRows = 32;
 
-template <int N>
-struct UpColsShape {  // floats of the sums of a pass of N values, per wave
-    static constexpr int NP = cols_red_floats(N);
-};
-
 inline size_t up_cols_lds_bytes(int ffn, int waves, int matrices, int B, bool from_mask)
 {
     return (from_mask ? (size_t)list_words_alloc(ffn / 64) * 8 : 0) +
            (size_t)waves * 4 * (kColsXFloats + kListPriv + 4 + kUpColsRows * matrices * cols_red_floats(B));
 }
 
-template <int B, int ACT, bool FROM_MASK, bool GLUE, int CPW, int R, bool SEQ = (CPW * B > 3)>
+template <int B, int ACT, bool FROM_MASK, bool GLUE, int CPW, int R, bool SEQ = (CPW * B > 3), int GT = B>
 __device__ __forceinline__ void up_cols_body(
     char *lds, const int bid, const int nblocks, const bool write_x, const __half *__restrict__ w_up,
     const __half *__restrict__ w_gate, const float *__restrict__ b_up, const float *__restrict__ x, const GlueIn gi,
@@ -271,18 +266,18 @@ __device__ __forceinline__ void up_cols_body(
         const rsrc_t sr = make_rsrc(gi.sign, (uint32_t)kSignRows * (uint32_t)gi.sstride);
         auto piece = [&](auto nyc) {
             constexpr int NY = decltype(nyc)::value;
-            ColGlue<B, NY> g[CPW];
+            if constexpr (!SEQ) {
+                ColGlue<B, NY> g[CPW];
 #pragma unroll
-            for (int c = 0; c < CPW; ++c) {
-                colglue_issue<B, NY>(g[c], xr, yr, sr, (uint32_t)gi.sstride, pbytes, (c * W + wave) * kChunk + lane * 4, d);
-                if (SEQ) {  // not enough registers for all of them at once
-                    colglue_commit<B, NY>(g[c], v[c], ss, lane);
-                    __builtin_amdgcn_sched_barrier(0);
-                }
-            }
-            if (!SEQ) {
+                for (int c = 0; c < CPW; ++c)
+                    colglue_issue<B, NY>(g[c], xr, yr, sr, (uint32_t)gi.sstride, pbytes, (c * W + wave) * kChunk + lane * 4, d);
 #pragma unroll
-                for (int c = 0; c < CPW; ++c) colglue_commit<B, NY>(g[c], v[c], ss, lane);
+                for (int c = 0; c < CPW; ++c) colglue_commit(g[c], v[c], ss, lane);
+            } else {  // not enough registers for all of them at once
+#pragma unroll
+                for (int c = 0; c < CPW; ++c)
+                    colglue_chunk<B, NY, GT>(v[c], ss, xr, yr, sr, (uint32_t)gi.sstride, pbytes,
+                                             (c * W + wave) * kChunk + lane * 4, d, lane);
             }
         };
         if (gi.ny == 4) piece(IntC<4>());
