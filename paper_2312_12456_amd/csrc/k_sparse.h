@@ -220,7 +220,7 @@ __global__ __launch_bounds__(kUpThreads) void k_up(
 // One workgroup per CU: with whole rows dealt to waves some CUs got half as many rows again as others.
 // One wave per row with x in LDS -> this, us: d 5120 gated, 2073 rows (42 MB) batch 1 12.4 -> 10.4, batch 2 18 ->
 // 14; d 4096 gated batch 3 14.7 -> 12.0; d 7168, 1700 rows 8.7 -> 8.3; d 4096, 1307 rows 5.9 -> 6.2 at
-// batch 1 (the whole call within 1 %).
+// batch 1 (which takes the former; the line is kUpColsMinElems).
 constexpr int kUpColsRows = 32;
 
 inline size_t up_cols_lds_bytes(int ffn, int waves, int matrices, int B, bool from_mask)

@@ -358,6 +358,15 @@ inline bool cols_ok(const pf_layer_desc &D, int B)
     return B <= 3 && D.d <= pf::kChunk * pf::kColsMaxWaves * (B == 3 ? 1 : 3);
 }
 
+// FC1 does so above this B * d only, gated layers over their own prediction at any: fewer waves are in flight per CU
+// at short rows, and a given list's share waits for the count where a wave per row can ask for its slot beside it.  us,
+// one wave per row / by column (FC1 and FC2 of 10 % of the neurons, then of 39 %, then of all): 768 x 2432 batch 1 7.5 /
+// 7.8, 8.4 / 8.8, 11.7 / 12.4; 2056 x 6528 batch 1 9.4 / 10.1, 14.0 / 15.1, 23.3 / 24.4; 4096 x 13056 batch 1 11.6 / 12.2,
+// 21.6 / 22.3, 43.0 / 44.1; 2056 x 6528 batch 2 (4112) 10.3 / 10.4, 15.0 / 15.5, 25.0 / 25.2.  Above the line, all neurons:
+// 2560 x 8192 batch 2 27.5 / 26.9, 5120 x 16384 batch 1 65.6 / 64.7, 6144 x 19648 95.1 / 96.8.  Layer steps, ungated,
+// 2056 x 6528 batch 1 at 15 % 17.7 / 17.8, gated 2056 x 6528 batch 2 22.0 / 20.9, 768 x 2432 batch 3 17.3 / 16.6 (4 %).
+constexpr int kUpColsMinElems = 4608;
+
 // Whether the vector output layer holds the hidden vector by column.
 inline bool out_cols_ok(const pf_layer_desc &D, int B) { return B <= 3 && D.r <= 4 * pf::kChunk; }
 
@@ -656,7 +665,7 @@ pf_status launch_sparse(pf_ctx *ctx, const pf_layer *L, const float *x, int B,
         else { PF_UPM(0, false, false); }
 #undef PF_UPM
     }
-    const bool cols = !mfma && cols_ok(D, B);
+    const bool cols = !mfma && cols_ok(D, B) && (B * D.d > kUpColsMinElems || (gated && from_mask));
     if (cols) {
         const int waves = pf::cols_waves(D.d), cpw = pf::cols_per_wave(D.d);
         const size_t lds = pf::up_cols_lds_bytes(D.ffn, waves, gated ? 2 : 1, B, from_mask);
