@@ -527,7 +527,9 @@ pf_status launch_predict(pf_ctx *ctx, const pf_layer *L, const float *x, const f
 // Row groups of FC2 (P): with `tiles` column tiles the launch has tiles * P workgroups, each
 // over 1/P of the listed rows.  One round of workgroups (<= one per CU) costs 1/P; two
 // workgroups share a CU at about 1.6 x the time of one up to batch 4 (measured at 112 and 128
-// tiles); more rounds cost a round each.  Ties go to the smaller P (fewer partial sums to add).
+// tiles); more rounds cost a round each.  int4 layers of 7 and 8 tokens run twice the workgroups (two halves of 4),
+// counted here as tiles: 12 layers, batch 7, by tiles / by workgroups, us: d 9216 782 / 707, 10240 845 / 754, 12288
+// 1031 / 1013, 4096 and 8192 the same.  Ties go to the smaller P (fewer partial sums to add).
 // From batch 5 on the vector form has the registers for one workgroup per CU only; k_down2_mfma has
 // room for two at any batch, but gains nothing from them there (steps of 6 layers, P = 2 / 4, us:
 // d 7168 batch 5 396 / 399, batch 8 424 / 428; d 8192 batch 5 359 / 364, batch 8 386 / 389).
@@ -600,12 +602,13 @@ pf_status launch_sparse_i4(pf_ctx *ctx, const pf_layer *L, const float *x, int B
     const int32_t *idx = from_mask ? ctx->idx : idx_in;
     const int32_t *count = from_mask ? ctx->count : count_in;
     const int tiles = cdiv(D.d, pf::kDown2I4Cols);
-    const int P = fc2_split(ctx, tiles, B);
+    const int halves = B > 6 ? 2 : 1;  // 7 and 8 tokens: twice the workgroups
+    const int P = fc2_split(ctx, tiles * halves, B);
     float *part = (ny_out || P > 1) ? ctx->ypart : y;
     {
         ProfScope ps(ctx, K_DOWN);
         PF_SWITCH_B(B, constexpr int NB = BT > 6 ? 4 : BT;
-                    PF_LAUNCH(ps, (pf::k_down2_i4<NB, pf::h_stride(BT)>), dim3(tiles, P, BT > 6 ? 2 : 1),
+                    PF_LAUNCH(ps, (pf::k_down2_i4<NB, pf::h_stride(BT)>), dim3(tiles, P, halves),
                               dim3(pf::kDown2I4Threads), 0, st, q_down, s_down, L->w.b_down, ctx->h, idx, count, part,
                               D.d, D.ffn, B));
     }

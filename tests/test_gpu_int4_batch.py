@@ -9,10 +9,10 @@ from tests.util import small_cfg
 pytestmark = pytest.mark.gpu
 
 
-@pytest.mark.parametrize("split", [1, 3])
+@pytest.mark.parametrize("split", [0, 1, 3])
 @pytest.mark.parametrize("act", [wl.ACT_RELU, wl.ACT_REGLU, wl.ACT_DRELU])
 @pytest.mark.parametrize("B,d,ffn", [(4, 128, 64), (5, 384, 448), (6, 1152, 1344), (7, 128, 64), (7, 1152, 1344),
-                                     (8, 384, 448), (8, 2176, 1344)])
+                                     (8, 384, 448), (8, 2176, 1344), (7, 8448, 192), (8, 12288, 192)])
 def test_int4_batch_against_single_tokens(B, d, ffn, act, split):
     from paper_2312_12456_amd import pf
     cfg = small_cfg(d=d, ffn=ffn, r=32, act=act, wtype=wl.W_INT4_G128, rate=0.3)
