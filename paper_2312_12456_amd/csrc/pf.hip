@@ -1138,12 +1138,13 @@ pf_status stack_enqueue_lookahead_merged(pf_ctx *ctx, pf_layer *const *layers, i
         ctx->last_idx = ctx->idx;
         ctx->last_count = ctx->count;
         const int tiles = cdiv(D.d, pf::kDown2Cols);
-        int P = ctx->down_split > 0 ? ctx->down_split : ctx->num_cu / tiles;
-        if (P < 1) P = 1;
-        // FC2 on about half of the CUs, the output layer's stream on the others; of a short list no more
+        int P = ctx->down_split;
+        // FC2 on about half of the CUs, the output layer's stream on the others (the next launch then reads 3
+        // instead of 5 vectors per workgroup at d = 4096); of a short list no more
         // parts than leave 1536 neurons each (us, P = 1 / 2 / 3 / 4: 3000 x 9600 batch 2 157 / 140 / 130 / 130,
-        // 2048 x 8192 162 / 138 / 136 / 136, 7B-class 623 / 547 / 566 / 577, 768 x 3072 110.6 / 110.1 / 111.1 / 112.7)
-        if (ctx->down_split == 0) P = std::max(1, std::min(cdiv(ctx->num_cu / 2, tiles), D.ffn / 1536));
+        // 2048 x 8192 162 / 138 / 136 / 136, 7B-class 623 / 547 / 566 / 577, 768 x 3072 110.6 / 110.1 / 111.1 / 112.7); three
+        // tokens want two parts of a list of that size already (768 x 2304 146 / 134 / 136 / 139, 768 x 3072 149 / 134 / 136 / 140)
+        if (ctx->down_split == 0) P = std::max(B == 3 && D.ffn >= 1536 ? 2 : 1, std::min(cdiv(ctx->num_cu / 2, tiles), D.ffn / 1536));
         // a single row group where the output layer beside it streams long enough to cover it
         // (measured: OPT-30B shape, 88 MB, +2 % at batch 1 and +4 % at batch 2; Falcon-40B shape,
         // 67 MB, even; OPT-6.7B shape, 34 MB, -10 %): the next launch then reads one vector less
