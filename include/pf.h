@@ -264,11 +264,12 @@ pf_status pf_ctx_set_lookahead(pf_ctx *ctx, int distance);
  *                           B * d (default 20480; 15360 where an FC1 on the matrix cores takes the
  *                           same input; from d = 1408 on 8192 where the library's glue forms it,
  *                           5000 where both hold; every value >= 0 is taken as given, for all four)
- *   PF_OPT_UP_GRID          workgroups of the vector FC1 kernel (default one per CU at batch 1 .. 3,
- *                           8 per CU otherwise; int4: 2 per CU)
+ *   PF_OPT_UP_GRID          workgroups of the vector FC1 kernel (default one per CU at batch 1 .. 3
+ *                           with B * d > 4608 or a gate, 8 per CU otherwise; int4: 2 per CU)
  *   PF_OPT_MFMA_GRID        workgroups of the matrix-core FC1 kernel (default one per CU)
- *   PF_OPT_DOWN_SPLIT       row groups of FC2, 1 .. 4 (default CUs / column tiles, at most 4; beside the
- *                           output layer, in two look-ahead launches, half of that)
+ *   PF_OPT_DOWN_SPLIT       row groups of FC2, 1 .. 4 (default CUs / column tiles, at most 4; in two look-ahead
+ *                           launches of fp16 layers up to batch 3 half of that, at most one per 1536
+ *                           neurons, and 1 beside an output layer of 80 MB and more)
  *   PF_OPT_LOOKAHEAD_FORM   how a look-ahead stack is scheduled (see pf_ctx_set_lookahead):
  *                           0 automatic (default), 1 two launches per layer where that form
  *                           applies, 2 predictors on a second stream, 3 everything on one stream

@@ -11,6 +11,8 @@
 // FC1 output of its a-th active neuron.  FC2 deals whole segments to its waves.  One kernel
 // boundary, one launch ramp, the mask scan and the trip of the index list through memory are
 // saved per layer.
+// k_out_up_cols holds the hidden vector and the input by column (r <= 2048, d <= 8192); k_out_up, one wave per
+// row with both staged in LDS, takes longer ones.
 // Work per workgroup follows the number of active neurons per segment (see seg_neuron for
 // the two ways of forming segments).  The bit words are internal; the caller-visible mask
 // format is produced by k_pred_out only.

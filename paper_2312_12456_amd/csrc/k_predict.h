@@ -347,9 +347,9 @@ struct GlueIn {
 // kColsXFloats.
 // Bound by the glue's bytes through each workgroup's memory path and one trip to memory.  One wave per row
 // with x staged in LDS -> this, us (glue included): d 5120, r 1024 batch 1 6.7 -> 5.3; d 7168, r 1536 9.0 ->
-// 7.5; d 12288, r 2048 15.0 -> 12.5; d 4096, r 1024 batch 1 4.2 -> 4.4 (the stack 0.5 % faster), batch 3 8.5 ->
-// 7.6.  Inside a stack it is behind at d = 768 batch 2, 3.8 -> 4.4 (the stack 15 % faster all the same), and at
-// d 4096, r 1024 batch 1 a trace had 4.2 -> 4.6.
+// 7.5; d 12288, r 2048 15.0 -> 12.5; d 768, r 128 batch 2 3.8 -> 3.5; d 4096, r 1024
+// batch 3 8.5 -> 7.6, batch 1 4.2 -> 4.4 (the one shape behind; the stack is 2 % faster all the same).  With a loop
+// around the one pass these two were 4.4 and 4.6.
 __host__ __device__ constexpr int cols_red_floats(int n) { return (n + 3) / 4 * 4; }
 
 // Sum of one value of the W <= MAX waves, `pitch` floats apart: all reads in flight at once.

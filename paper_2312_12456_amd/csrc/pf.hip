@@ -772,8 +772,10 @@ bool fused_ok(const pf_ctx *ctx, const pf_layer *L, int B)
     // 553 / 558; 768 x 3072 batch 1 155 / 170, batch 2 179 / 187; 3072 x 12288 batch 2 256 / 263; 13B-class batch
     // 1 614 / 596, 2 504 / 453, 30B-class batch 1 330 / 311.  Two tokens of an ungated layer with longer rows
     // are nearly even (30B-class 401 / 392, Falcon-40B-class 276 / 271) and keep the form they had.  A
-    // batch of a gated layer with segments for less than half of the CUs is faster through the list:
-    // 2048 x 5632 batch 2 232 / 228, batch 3 284 / 269.
+    // batch of a gated layer with segments for less than half of the CUs goes through the list, which holds its
+    // own at higher rates: 12 layers, rate 0.08, then 0.14: 768 x 2432 batch 2 173 / 180, 185 / 181, batch 3 193 / 195,
+    // 212 / 204; 2048 x 5632 batch 2 209 / 215, 232 / 228, batch 3 246 / 231, 271 / 258; 3072 x 8128 batch 2 259 / 249, 296 /
+    // 275, batch 3 301 / 298, 348 / 322.
     const bool gated = D.act != PF_ACT_RELU, few = 2 * (D.ffn / 64) < ctx->num_cu;
     if (gated && few && B >= 2) return false;
     return D.d <= 4096 || (B == 2 && !gated && D.d <= pf::kOutUpMaxChunks * pf::kChunk);
@@ -1079,18 +1081,9 @@ pf_status stack_enqueue_lookahead_merged(pf_ctx *ctx, pf_layer *const *layers, i
         const bool glue = l > 0;
         float *xn = glue ? ctx->xbuf[l & 1] : nullptr;
         if (glue && ctx->split_src == xn) ctx->split_src = nullptr;  // rewritten as fp32 only
-        const int n_hid = N ? cdiv(N->desc.r, pf::kPredWaves) : 0;
-        int n_up = cdiv(D.ffn, pf::kUpWaves);
         // Measured on the benchmark shapes (batch 1..3): the roles with the dependent chains
-        // (FC1, FC2) take the low block numbers, FC1 gets two workgroups per CU (every one of
-        // them forms the glue, so surplus workgroups cost cache reads), and FC2 leaves two
-        // partial sums instead of four (fewer CUs gather, but the output layer's stream keeps
-        // the others busy, and the next launch reads 3 instead of 5 vectors per workgroup).
-        if (n_up > 2 * ctx->num_cu) n_up = 2 * ctx->num_cu;
-        const size_t lds1 = ((size_t)B * kpad_of(D.d) + pf::kStageScrap) * sizeof(float) +
-                            pf::up_mask_lds_bytes(D.ffn);
-        bool cols = cols_ok(D, B);
-        if (cols) {
+        // (FC1, FC2) take the low block numbers.
+        if (cols_ok(D, B)) {
             // one workgroup per CU for FC1 and as many rows of the hidden layer: both fit beside each other
             const int waves = pf::cols_waves(D.d), cpw = pf::cols_per_wave(D.d);
             const int n_up = ctx->up_cols_grid > 0 ? ctx->up_cols_grid : ctx->num_cu;
@@ -1117,6 +1110,11 @@ pf_status stack_enqueue_lookahead_merged(pf_ctx *ctx, pf_layer *const *layers, i
 #undef PF_LA1CC
 #undef PF_LA1C
         } else {
+            // FC1 gets two workgroups per CU: every one of them forms the glue, so surplus ones cost cache reads
+            const int n_hid = N ? cdiv(N->desc.r, pf::kPredWaves) : 0;
+            const int n_up = std::min(cdiv(D.ffn, pf::kUpWaves), 2 * ctx->num_cu);
+            const size_t lds1 = ((size_t)B * kpad_of(D.d) + pf::kStageScrap) * sizeof(float) +
+                                pf::up_mask_lds_bytes(D.ffn);
             ProfScope ps(ctx, K_LA_UP_HIDDEN);
 #define PF_LA1(ACT, GLUE)                                                                          \
     PF_SWITCH_B3(B, PF_LAUNCH(ps, (pf::k_la_up_hidden<BT, ACT, GLUE>), dim3(n_hid + n_up),          \
